@@ -7,6 +7,13 @@
 // the FP64 true residual |phi - Q x| / |phi| <= tol, and when the iterated
 // residual meets tol but the true one does not, the iteration continues from
 // the true residual keeping p.
+//
+// An iteration is bound by its serial chain: four barriers, two LDS stencils
+// and two sums.  The lane's own p and M p and both of its links stay in
+// registers (six LDS reads a site in d = 1 instead of ten), the number of
+// dimensions and the sites per lane are constants, and the sums are register
+// moves (wave_sum): d = 1 32 x 64 took 2.45 us an iteration with the sums as
+// LDS permutes and the links in LDS, and takes 1.39 us.
 #include <cmath>
 
 #include "internal.h"
@@ -16,8 +23,8 @@ namespace hub {
 namespace {
 
 constexpr int kSB = 512;                   // lanes of the block (8 waves: measured faster than 4 or 16)
-constexpr int kNPT = 4;                    // sites per lane
-constexpr int kSmallSitesMax = kSB * kNPT;
+constexpr int kNPTMax = 4;                 // sites per lane of the largest lattice
+constexpr int kSmallSitesMax = kSB * kNPTMax;
 
 struct SmallResult {
     int32_t iters;
@@ -50,71 +57,75 @@ struct BlockSum {
     }
 };
 
+// What a lane keeps of one of its sites: LDS indices of the neighbours, and
+// the two links that its M and M^T rows read.
+template <int D>
 struct Site {
-    int i;        // linear index (0 for a lane past the end)
-    bool ok;      // i < V
-    int nb[6];    // spatial neighbours +-e_j, j < d
-    int im, ip;   // same n on slice s-1 and s+1 (periodic in the index)
+    int i;           // linear index (0 for a lane past the end)
+    bool ok;         // i < V
+    int nb[2 * D];   // spatial neighbours +-e_j
+    int im, ip;      // same n on slice s-1 and s+1 (periodic in the index)
+    double a, ap;    // A_{n,s}, A_{n,s+1}
 };
 
-__device__ inline Site make_site(const Geom& g, int i) {
-    Site S;
+template <int D>
+__device__ inline Site<D> make_site(const Geom& g, int i, const double* __restrict__ A) {
+    Site<D> S;
     S.ok = i < g.V;
     S.i = S.ok ? i : 0;
     const int n = S.i % g.vs, s = S.i / g.vs;
     int stride = 1;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        if (j < g.d) {
-            const int c = (n / stride) % g.nx;
-            const int cp = c + 1 == g.nx ? 0 : c + 1;
-            const int cm = c == 0 ? g.nx - 1 : c - 1;
-            S.nb[2 * j] = S.i + (cp - c) * stride;
-            S.nb[2 * j + 1] = S.i + (cm - c) * stride;
-            stride *= g.nx;
-        } else {
-            S.nb[2 * j] = S.nb[2 * j + 1] = S.i;
-        }
+    for (int j = 0; j < D; ++j) {
+        const int c = (n / stride) % g.nx;
+        const int cp = c + 1 == g.nx ? 0 : c + 1;
+        const int cm = c == 0 ? g.nx - 1 : c - 1;
+        S.nb[2 * j] = S.i + (cp - c) * stride;
+        S.nb[2 * j + 1] = S.i + (cm - c) * stride;
+        stride *= g.nx;
     }
     S.im = n + g.vs * (s == 0 ? g.nt - 1 : s - 1);
     S.ip = n + g.vs * (s + 1 == g.nt ? 0 : s + 1);
+    S.a = A[S.i];
+    S.ap = A[S.ip];
     return S;
 }
 
-// (M v)_i = v_i - kappa sum_j (v_{i+e_j} + v_{i-e_j}) + A_i v_{i, s-1}
-__device__ inline double apply_M_at(const Geom& g, const Site& S, const double* v,
-                                    const double* A) {
+// (M v)_i = v_i - kappa sum_j (v_{i+e_j} + v_{i-e_j}) + A_i v_{i, s-1}; vi is
+// the lane's own v_i.
+template <int D>
+__device__ inline double apply_M_at(const Geom& g, const Site<D>& S, double vi,
+                                    const double* v) {
     double hop = 0.0;
 #pragma unroll
-    for (int j = 0; j < 6; ++j)
-        if (j < 2 * g.d) hop += v[S.nb[j]];
-    return v[S.i] - g.kappa * hop + A[S.i] * v[S.im];
+    for (int j = 0; j < 2 * D; ++j) hop += v[S.nb[j]];
+    return vi - g.kappa * hop + S.a * v[S.im];
 }
 
 // (M^T v)_i = v_i - kappa sum_j (v_{i+e_j} + v_{i-e_j}) + A_{i, s+1} v_{i, s+1}
-__device__ inline double apply_Mt_at(const Geom& g, const Site& S, const double* v,
-                                     const double* A) {
+template <int D>
+__device__ inline double apply_Mt_at(const Geom& g, const Site<D>& S, double vi,
+                                     const double* v) {
     double hop = 0.0;
 #pragma unroll
-    for (int j = 0; j < 6; ++j)
-        if (j < 2 * g.d) hop += v[S.nb[j]];
-    return v[S.i] - g.kappa * hop + A[S.ip] * v[S.ip];
+    for (int j = 0; j < 2 * D; ++j) hop += v[S.nb[j]];
+    return vi - g.kappa * hop + S.ap * v[S.ip];
 }
 
+template <int D, int kNPT>
 __global__ __launch_bounds__(kSB) void k_cg_small(Geom g, const double* __restrict__ A,
                                                   const double* __restrict__ phi,
                                                   double* __restrict__ x_out, double tol2,
                                                   int max_iter, SmallResult* res) {
-    __shared__ double P[kSmallSitesMax], Y[kSmallSitesMax], AL[kSmallSitesMax];
+    __shared__ double P[kSB * kNPT], Y[kSB * kNPT];
     __shared__ double red[2 * (kSB / 64)];
     BlockSum sum_block{red, 0};
-    Site S[kNPT];
+    Site<D> S[kNPT];
     double x[kNPT], r[kNPT], p[kNPT], f[kNPT];
 #pragma unroll
     for (int k = 0; k < kNPT; ++k) {
-        S[k] = make_site(g, threadIdx.x + kSB * k);
+        S[k] = make_site<D>(g, threadIdx.x + kSB * k, A);
         f[k] = S[k].ok ? phi[S[k].i] : 0.0;
-        if (S[k].ok) AL[S[k].i] = A[S[k].i];
         x[k] = 0.0;
         r[k] = f[k];
         p[k] = f[k];
@@ -125,15 +136,18 @@ __global__ __launch_bounds__(kSB) void k_cg_small(Geom g, const double* __restri
         for (int k = 0; k < kNPT; ++k)
             if (S[k].ok) P[S[k].i] = v[k];
         __syncthreads();
+        double y[kNPT];
 #pragma unroll
-        for (int k = 0; k < kNPT; ++k)
-            if (S[k].ok) Y[S[k].i] = apply_M_at(g, S[k], P, AL);
+        for (int k = 0; k < kNPT; ++k) {
+            y[k] = apply_M_at(g, S[k], v[k], P);
+            if (S[k].ok) Y[S[k].i] = y[k];
+        }
         __syncthreads();
         double part = 0.0;
 #pragma unroll
         for (int k = 0; k < kNPT; ++k) {
             if (S[k].ok) {
-                const double d = f[k] - apply_Mt_at(g, S[k], Y, AL);
+                const double d = f[k] - apply_Mt_at(g, S[k], y[k], Y);
                 r[k] = d;
                 part += d * d;
             }
@@ -154,15 +168,18 @@ __global__ __launch_bounds__(kSB) void k_cg_small(Geom g, const double* __restri
         for (int k = 0; k < kNPT; ++k)
             if (S[k].ok) P[S[k].i] = p[k];
         __syncthreads();
+        double y[kNPT], q[kNPT];
 #pragma unroll
-        for (int k = 0; k < kNPT; ++k)
-            if (S[k].ok) Y[S[k].i] = apply_M_at(g, S[k], P, AL);
+        for (int k = 0; k < kNPT; ++k) {
+            y[k] = apply_M_at(g, S[k], p[k], P);
+            if (S[k].ok) Y[S[k].i] = y[k];
+        }
         __syncthreads();
-        double q[kNPT];
         part = 0.0;
 #pragma unroll
         for (int k = 0; k < kNPT; ++k) {
-            q[k] = S[k].ok ? apply_Mt_at(g, S[k], Y, AL) : 0.0;
+            const double z = apply_Mt_at(g, S[k], y[k], Y);
+            q[k] = S[k].ok ? z : 0.0;
             part += p[k] * q[k];
         }
         const double pq = sum_block(part);
@@ -227,6 +244,28 @@ __global__ __launch_bounds__(kSB) void k_cg_small(Geom g, const double* __restri
     }
 }
 
+// Every lane takes as few sites as cover the lattice: a site more is two more
+// stencils in the chain of every iteration, also where it lies past the end.
+template <int D>
+void launch_small_d(const Geom& g, const double* A, const double* phi, double* x, double tol2,
+                    int max_iter, SmallResult* res, hipStream_t st) {
+    if (g.V <= kSB)
+        k_cg_small<D, 1><<<1, kSB, 0, st>>>(g, A, phi, x, tol2, max_iter, res);
+    else if (g.V <= 2 * kSB)
+        k_cg_small<D, 2><<<1, kSB, 0, st>>>(g, A, phi, x, tol2, max_iter, res);
+    else
+        k_cg_small<D, kNPTMax><<<1, kSB, 0, st>>>(g, A, phi, x, tol2, max_iter, res);
+}
+
+void launch_small(const Geom& g, const double* A, const double* phi, double* x, double tol2,
+                  int max_iter, SmallResult* res, hipStream_t st) {
+    switch (g.d) {
+        case 1: launch_small_d<1>(g, A, phi, x, tol2, max_iter, res, st); break;
+        case 2: launch_small_d<2>(g, A, phi, x, tol2, max_iter, res, st); break;
+        default: launch_small_d<3>(g, A, phi, x, tol2, max_iter, res, st); break;
+    }
+}
+
 }  // namespace
 
 bool cg_small_fits(const Geom& g) { return g.V <= kSmallSitesMax; }
@@ -251,7 +290,7 @@ hub_status cg_solve_small(const Geom& g, const double* sigma, const double* phi,
     step(hipEventCreate(&t1));
     if (r == HUB_OK) {
         step(hipEventRecord(t0, st));
-        k_cg_small<<<1, kSB, 0, st>>>(g, A, phi, x, o.tol * o.tol, o.max_iter, dres);
+        launch_small(g, A, phi, x, o.tol * o.tol, o.max_iter, dres, st);
         step(hipGetLastError());
         step(hipEventRecord(t1, st));
         step(hipMemcpyAsync(&h, dres, sizeof(h), hipMemcpyDeviceToHost, st));

@@ -104,10 +104,49 @@ __device__ inline int wrap1(int v, int n) {
     return v < 0 ? v + n : (v >= n ? v - n : v);
 }
 
-// Sum over a 64-wide wavefront, result valid in every lane.
+// v of the lane that a DPP control names (all lanes have a source there).
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    const long long w = __builtin_bit_cast(long long, v);
+    const int lo = (int)w, hi = (int)(w >> 32);
+    const int rlo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    const int rhi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)(unsigned)rhi << 32) |
+                                                  (unsigned)rlo));
+}
+
+// v_i + v_{i xor 32} (HALF = 32) or v_i + v_{i xor 16} (HALF = 16): the swap
+// of two copies of v leaves one addend of every lane in each copy.
+template <int HALF>
+__device__ __forceinline__ double swap_add(double v) {
+    const long long w = __builtin_bit_cast(long long, v);
+    const unsigned lo = (unsigned)w, hi = (unsigned)(w >> 32);
+    auto sw = [](unsigned x) {
+        if constexpr (HALF == 32) return __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        else return __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    };
+    const auto l = sw(lo), h = sw(hi);
+    const double a = __builtin_bit_cast(
+        double, (long long)(((unsigned long long)h[0] << 32) | l[0]));
+    const double b = __builtin_bit_cast(
+        double, (long long)(((unsigned long long)h[1] << 32) | l[1]));
+    return a + b;
+}
+
+// Sum over a 64-wide wavefront, result valid in every lane.  The tree of the
+// xor butterfly (32, 16, 8, 4, 2, 1), whose every step adds the same two
+// numbers in all lanes that share them, so that its bits do not depend on how
+// the numbers travel: as register moves (lane swaps, DPP rotations and quad
+// permutations) a step costs a few cycles, as an LDS permute a round trip of
+// over a hundred.  After the step of 8 the values repeat every 8 lanes of a
+// row, so a rotation by 4 brings the lane of i xor 4.
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    v = swap_add<32>(v);
+    v = swap_add<16>(v);
+    v += dpp_move<0x128>(v);  // row_ror:8
+    v += dpp_move<0x124>(v);  // row_ror:4
+    v += dpp_move<0x4e>(v);   // quad_perm 2,3,0,1
+    v += dpp_move<0xb1>(v);   // quad_perm 1,0,3,2
     return v;
 }
 

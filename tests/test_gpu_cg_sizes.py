@@ -1,0 +1,49 @@
+"""FP64 hub_cg_solve at the edges of its one-workgroup kernels: one, two and
+four sites per lane of 512 lanes, full and with a remainder, in each number of
+dimensions.  Checked as in test_gpu_cg.py: the oracle's true residual, the
+distance to the oracle's solution (two solutions with residual <= tol differ
+by at most 2 cond(Q) tol; twice that for the Lanczos estimate of cond(Q)), and
+the iteration count."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1007_3432_amd import hub, inputs
+from tests import dense, hubtest
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-10
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    hubtest.ensure_built()
+    oracle.set_threads(16)
+
+
+def check(shape):
+    olat, lat = oracle.Lattice(*shape), hub.lattice(*shape)
+    hubtest.log_case(f"cg sizes {shape}")
+    sigma, eta = inputs.sigma_eta(*shape, seed=11)
+    A = oracle.links(olat, sigma)
+    phi = oracle.apply_Mt(olat, A, eta)
+    x_o, res, (al, be) = oracle.cg(olat, A, phi, tol=TOL, record=True)
+    assert res.converged
+    x_d = hubtest.empty(lat.volume, hub.F64)
+    st = hub.hub_cg_solve(lat, hubtest.to_dev(sigma), hubtest.to_dev(phi), x_d, hub.cg_opts(hub.F64))
+    x = x_d.cpu().numpy()
+    assert st["status"] == "HUB_OK"
+    r = np.linalg.norm(phi - oracle.apply_MtM(olat, A, x)) / np.linalg.norm(phi)
+    assert r <= 1.1 * TOL
+    assert hubtest.rel_err(x, x_o) <= 4 * dense.lanczos_condition(al, be) * TOL
+    assert abs(st["iters"] - res.iters) <= 0.03 * res.iters + 3
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 16, 32), (1, 27, 19), (1, 32, 32), (1, 205, 5), (1, 64, 32), (2, 8, 8), (2, 5, 21),
+    (2, 2, 129), (2, 32, 2), (2, 18, 6), (3, 8, 2), (3, 2, 66), (3, 4, 32), (3, 3, 75)],
+    ids=lambda s: "d%d_%dx%d" % s)
+def test_one_workgroup(shape):
+    assert shape[1] ** shape[0] * shape[2] <= 2048
+    check(shape)
