@@ -128,10 +128,13 @@ HUB_API hub_status hub_apply_MtM(const hub_lattice* lat, const void* links,
  *   the iterated residual meets tol) x += x_lo is folded into the FP64
  *   solution and r is replaced by the FP64 true residual phi - Q x.
  * Convergence is always decided on the FP64 true residual.  With bulk =
- * HUB_F64 on a lattice of at most 2048 sites the whole solve runs in one
- * workgroup (one kernel launch, no graphs); otherwise each iteration is a few
- * kernels replayed in chunks from HIP graphs.  The device workspace (about
- * five V-vectors of `bulk` plus the links) and the chunk graphs are kept per
+ * HUB_F64 a lattice of at most 2048 sites is solved in one workgroup (one
+ * kernel launch), and one that fits the registers of the chip (up to about a
+ * million sites: nx^(d-1) at most 512) by one block per CU, a launch per 1000
+ * iterations; such launches of several threads follow each other.  (In the
+ * latter the sums are arranged after Chronopoulos and Gear.)  Otherwise each
+ * iteration is a few kernels replayed in chunks from HIP graphs.  The device
+ * workspace (about six V-vectors) and the chunk graphs are kept per
  * host thread after the call: the next solve on that thread reuses the
  * workspace when it is large enough (else frees it and allocates a larger
  * one, which synchronizes the device) and replays the graphs when lattice,

@@ -478,6 +478,12 @@ hub_status solve(const Geom& g, const double* sigma, const double* phi, double* 
     // then bound by barriers, not by three kernel launches.
     if (!mixed && !cheb && cg_small_fits(g)) return cg_solve_small(g, sigma, phi, x, o, out, st);
     HUB_TRY(g_ctx.ensure());
+    // One whose vectors fit the registers of the chip stays there.
+    if (!mixed && !cheb) {
+        bool ran = false;
+        const hub_status r = cg_solve_resident(g, sigma, phi, x, o, out, st, &ran);
+        if (ran || r != HUB_OK) return r;
+    }
     const size_t V = (size_t)g.V;
     const size_t vb = mixed ? 4 : 8;
     const SweepPlan P = plan_sweep(g, !mixed, true);
@@ -587,6 +593,12 @@ hub_status solve(const Geom& g, const double* sigma, const double* phi, double* 
 hub_status solver_workspace(size_t bytes, char** out) {
     HUB_TRY(g_ctx.ensure());
     return g_ctx.workspace(bytes, out);
+}
+
+hub_status solver_host(SolverHost* out) {
+    HUB_TRY(g_ctx.ensure());
+    *out = {g_ctx.snap, g_ctx.t0, g_ctx.t1};
+    return HUB_OK;
 }
 
 // Nothing of this thread's runs on the context stream: every solve waits

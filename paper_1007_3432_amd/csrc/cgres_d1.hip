@@ -1,0 +1,6 @@
+// Resident CG kernels for d = 1 (cgres.h).
+#include "cgres.h"
+
+namespace hub {
+ResKernel res_kernel_d1(int level, bool whole) { return res_kernel_d<1>(level, whole); }
+}  // namespace hub

@@ -1,0 +1,6 @@
+// Resident CG kernels for d = 3 (cgres.h).
+#include "cgres.h"
+
+namespace hub {
+ResKernel res_kernel_d3(int level, bool whole) { return res_kernel_d<3>(level, whole); }
+}  // namespace hub

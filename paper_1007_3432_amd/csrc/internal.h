@@ -1,6 +1,7 @@
 // Host-side internals of libhub shared between translation units.
 #pragma once
 
+#include <mutex>
 #include <string>
 
 #include "common.h"
@@ -62,6 +63,22 @@ void solver_release();
 bool cg_small_fits(const Geom& g);
 hub_status cg_solve_small(const Geom& g, const double* sigma, const double* phi, double* x,
                           const hub_cg_opts& o, hub_cg_stats* out, hipStream_t st);
+
+// The calling thread's pinned snapshot buffer (two CGScalars) and timing
+// events (cg.hip), for one solve at a time.
+struct SolverHost {
+    CGScalars* snap;
+    hipEvent_t t0, t1;
+};
+hub_status solver_host(SolverHost* out);
+
+// FP64 CG resident on the chip (cgres.hip).  *ran = false, and nothing solved,
+// when the lattice or the device does not allow it or a wait between blocks
+// was given up; x and the workspace may have been written then.
+hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* phi, double* x,
+                             const hub_cg_opts& o, hub_cg_stats* out, hipStream_t st, bool* ran);
+// Held while a kernel whose blocks wait for each other runs on the device.
+std::mutex& resident_mutex(int device);
 
 // HMC (hmc.hip; arguments already validated).
 hub_status hmc_force(const Geom& g, const double* sigma, const double* x, double* F,

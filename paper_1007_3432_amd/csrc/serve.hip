@@ -764,6 +764,7 @@ hub_status run_epoch(hub_server* S) {
     HUB_HIP(hipMemcpyAsync(S->desc_d, S->desc_h, sizeof(SlotDesc) * n, hipMemcpyHostToDevice,
                            S->stream));
     int iters = S->opts.cg.reliable_every;
+    std::unique_lock<std::mutex> resident;
     const SlotDesc* descp = S->desc_d;
     const bool f16 = S->opts.cg.link == HUB_F16;
     if (S->opts.engine == 1) {
@@ -785,6 +786,9 @@ hub_status run_epoch(hub_server* S) {
                         (void*)&tot_elem, (void*)&ctl, (void*)&spin_limit};
         const void* fn = f16 ? (const void*)k_serve_epoch<Link16>
                              : (const void*)k_serve_epoch<Link32>;
+        // Until the kernel has ended (below), no other one whose blocks wait
+        // for each other may take CUs from it.
+        resident = std::unique_lock<std::mutex>(resident_mutex(S->device));
         HUB_HIP(hipLaunchCooperativeKernel(fn, dim3(S->coop_grid), dim3(256), args,
                                            kServeLdsBytes, S->stream));
     } else {
@@ -820,6 +824,7 @@ hub_status run_epoch(hub_server* S) {
     HUB_HIP(hipMemcpyAsync(S->ctl_h, S->ctl_d, sizeof(EpochCtl), hipMemcpyDeviceToHost,
                            S->stream));
     HUB_HIP(hipStreamSynchronize(S->stream));
+    if (resident.owns_lock()) resident.unlock();
     if (S->opts.engine == 1 && S->ctl_h->abort)
         return set_error(HUB_E_DEVICE, "serving kernel: a grid barrier timed out");
     for (int k : ks)

@@ -1,9 +1,11 @@
-"""FP64 hub_cg_solve at the edges of its one-workgroup kernels: one, two and
-four sites per lane of 512 lanes, full and with a remainder, in each number of
-dimensions.  Checked as in test_gpu_cg.py: the oracle's true residual, the
+"""FP64 hub_cg_solve at the edges of its kernels: one, two and four sites per
+lane of one workgroup, full and with a remainder, in each number of dimensions,
+and the resident solver's cuts.  Checked as in test_gpu_cg.py: the oracle's true residual, the
 distance to the oracle's solution (two solutions with residual <= tol differ
 by at most 2 cond(Q) tol; twice that for the Lanczos estimate of cond(Q)), and
 the iteration count."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -47,3 +49,51 @@ def check(shape):
 def test_one_workgroup(shape):
     assert shape[1] ** shape[0] * shape[2] <= 2048
     check(shape)
+
+
+# The resident solver: z whole and cut, tiles of unequal size, one slice and
+# several per block, inner planes that leave lanes idle, every level.
+@pytest.mark.parametrize("shape", [
+    (1, 37, 60), (1, 257, 33), (1, 5000, 7), (1, 3, 900), (1, 2048, 200), (2, 33, 20), (2, 5, 100),
+    (2, 512, 2), (2, 300, 3), (2, 47, 47), (3, 5, 20), (3, 9, 17), (3, 2, 300), (3, 16, 12),
+    (3, 20, 6), (3, 22, 3), (3, 12, 50)],
+    ids=lambda s: "d%d_%dx%d" % s)
+def test_resident(shape):
+    assert shape[1] ** shape[0] * shape[2] > 2048
+    check(shape)
+
+
+def test_resident_wait_given_up(monkeypatch):
+    """With a single read allowed, blocks give up the first wait for each
+    other: the solve ends and is done by the multi-kernel solver."""
+    monkeypatch.setenv("HUB_CG_RESIDENT_READS", "1")
+    check((1, 256, 32))
+
+
+def test_resident_threads():
+    """Two threads that solve at the same time get what each gets alone."""
+    import torch
+    probs, alone, both = [], [], [None, None]
+    for shape in ((3, 8, 24), (1, 300, 40)):
+        lat = hub.lattice(*shape)
+        sigma, phi = inputs.sigma_eta(*shape, seed=12)
+        probs.append((lat, hubtest.to_dev(sigma), hubtest.to_dev(phi)))
+
+    def solve(k, stream):
+        lat, sigma, phi = probs[k]
+        x = hubtest.empty(lat.volume, hub.F64)
+        with torch.cuda.stream(stream):
+            for _ in range(3):
+                hub.hub_cg_solve(lat, sigma, phi, x, hub.cg_opts(hub.F64))
+        return x.cpu().numpy()
+
+    streams = [torch.cuda.Stream() for _ in probs]
+    alone = [solve(k, streams[k]) for k in range(2)]
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=lambda k=k: both.__setitem__(k, solve(k, streams[k]))) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for a, b in zip(alone, both):
+        assert b is not None and np.array_equal(a, b)
