@@ -231,7 +231,9 @@ hub_status noalloc_scratch(double** out) {
 size_t cheb_noalloc_bytes(const Geom& g) {
     const SweepPlan P = plan_sweep(g, true);
     const size_t vb = ((size_t)g.V * 8 + 255) & ~size_t(255);
-    return vb * (P.fused ? 1 : 2);
+    // One vector for the d = 1 and d = 3 tiles, two for the rest: the sizes
+    // that callers are told, also where the sweep needs only one.
+    return vb * (P.kind == kSweepD1 || P.kind == kSweepD3 ? 1 : 2);
 }
 
 hub_status cheb_apply_noalloc(const Geom& g, const double* links, const double* r, double* z,

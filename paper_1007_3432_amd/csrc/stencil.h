@@ -1115,6 +1115,241 @@ __global__ __launch_bounds__(BLOCK) void k_mtm_d3(Geom g, Op op, int tiles_y, in
 }
 
 // ---------------------------------------------------------------------------
+// Fused Q = M^T M sweep for d = 2 and 3 and any nx whose rows fit.
+//
+// The march of tile_mtm_d3 with the extents as run-time values: a block owns
+// ty x tz whole x rows (d = 2: ty rows) of a slice, the lattice being cut into
+// tiles_y x tiles_z tiles of nearly equal size, and steps through tc slices.
+// Halo rows are those that the stencils reach (distance 2 for X, 1 for Y, no
+// corners).  A lane handles up to NC owned sites and NHX, NHY halo sites; a
+// position past the end repeats the last one, writes to the spare LDS element
+// and leaves the op alone.  The coordinates cost some divisions per block, not
+// per slice.  Latency-bound like tile_mtm_d3 (two barriers and a loaded memory
+// round trip a slice); two passes over memory and a scratch vector before.
+// FP64 and FP32 products, us, before and now: d = 2 33^2 x 60 21.1 and 4.2,
+// 21.5 and 3.9; 64^2 x 145 22.6 and 6.6, 22.0 and 5.3; 128^2 x 512 104 and 54,
+// 60.7 and 24.8; d = 3 20^3 x 96 23.4 and 7.9, 21.5 and 6.7; 48^3 x 48 76.0
+// and 42.2, 51.4 and 23.3 (of the smaller ones' time before, some 10 us was
+// the allocation of the scratch vector).
+template <int D>
+__host__ __device__ constexpr int rows_halo_x(int ty, int tz) {
+    return D == 3 ? 4 * ty + 4 * tz + 4 : 4;
+}
+template <int D>
+__host__ __device__ constexpr int rows_halo_y(int ty, int tz) {
+    return D == 3 ? 2 * ty + 2 * tz : 2;
+}
+template <int D>
+__host__ __device__ constexpr int rows_lds_elems(int nx, int ty, int tz) {
+    return nx * ((ty + 4) * (D == 3 ? tz + 4 : 1) + (ty + 2) * (D == 3 ? tz + 2 : 1)) + 1;
+}
+
+template <class Op, int D, int NC, int NHX, int NHY, int BLOCK>
+__device__ __forceinline__ void tile_mtm_rows(const Geom& g, const Op& op, int tiles_y,
+                                              int tiles_z, int tc, int b,
+                                              typename Op::acc_t* lds,
+                                              double (&part)[Op::kNP]) {
+    static_assert(D == 2 || D == 3, "d = 1 has no rows");
+    using Acc = typename Op::acc_t;
+    using Center = typename Op::center_t;
+    constexpr int HZ = D == 3 ? 1 : 0;
+    const int nx = g.nx, nt = g.nt, vs = g.vs;
+    const int iy = b % tiles_y;
+    b /= tiles_y;
+    const int iz = D == 3 ? b % tiles_z : 0;
+    const int ch = D == 3 ? b / tiles_z : b;
+    const int y0 = iy * nx / tiles_y, ty = (iy + 1) * nx / tiles_y - y0;
+    const int z0 = D == 3 ? iz * nx / tiles_z : 0;
+    const int tz = D == 3 ? (iz + 1) * nx / tiles_z - z0 : 1;
+    const int s0 = ch * tc, h = min(tc, nt - s0);
+    const int XY = ty + 4, YY = ty + 2;
+    const int PX = nx * XY * (tz + 4 * HZ);
+    Acc* X = lds;
+    Acc* Y = lds + PX;
+    const int sink = PX + nx * YY * (tz + 2 * HZ);  // spare element, index into lds
+    const int t = threadIdx.x;
+    const Acc kappa = (Acc)g.kappa;
+    const int own = nx * ty * tz;
+    const int nhx = nx * rows_halo_x<D>(ty, tz), nhy = nx * rows_halo_y<D>(ty, tz);
+
+    // Owned sites: spatial index, X and Y index, offsets of the x neighbours.
+    int cn[NC], cxi[NC], cyi[NC], cup[NC], cdn[NC];
+    bool cok[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        int q = t + BLOCK * k;
+        cok[k] = q < own;
+        if (!cok[k]) q = own - 1;
+        const int row = fdiv(q, g.fnx), x = q - row * nx;
+        const int zz = row / ty, yy = row - zz * ty;
+        cn[k] = x + nx * ((y0 + yy) + nx * (z0 + zz));
+        cxi[k] = x + nx * ((yy + 2) + XY * (zz + 2 * HZ));
+        cyi[k] = x + nx * ((yy + 1) + YY * (zz + HZ));
+        cup[k] = x + 1 == nx ? 1 - nx : 1;
+        cdn[k] = x == 0 ? nx - 1 : -1;
+    }
+    // X halo: rows at z distance 2 over ty rows, at distance 1 over ty + 2,
+    // and two rows on each side in y.
+    int hxs[NHX], hxi[NHX];
+#pragma unroll
+    for (int k = 0; k < NHX; ++k) {
+        int q = t + BLOCK * k;
+        const bool ok = q < nhx;
+        if (!ok) q = nhx - 1;
+        int r = fdiv(q, g.fnx);
+        const int x = q - r * nx;
+        int yx, zx;  // row in X
+        if constexpr (D == 2) {
+            yx = r < 2 ? r : ty + r;
+            zx = 0;
+        } else if (r < 2 * ty) {
+            zx = r < ty ? 0 : tz + 3;
+            yx = 2 + (r < ty ? r : r - ty);
+        } else if (r < 4 * ty + 4) {
+            r -= 2 * ty;
+            zx = r < ty + 2 ? 1 : tz + 2;
+            yx = 1 + (r < ty + 2 ? r : r - ty - 2);
+        } else {
+            r -= 4 * ty + 4;
+            zx = 2 + (r >> 2);
+            yx = (r & 3) < 2 ? (r & 3) : ty + (r & 3);
+        }
+        hxi[k] = ok ? x + nx * (yx + XY * zx) : sink;
+        hxs[k] = x + nx * (wrap1(y0 - 2 + yx, nx) + (D == 3 ? nx * wrap1(z0 - 2 + zx, nx) : 0));
+    }
+    // Y halo: rows at z distance 1 over ty rows, and one on each side in y.
+    int hys[NHY], hyi[NHY], hyx[NHY], hup[NHY], hdn[NHY];
+#pragma unroll
+    for (int k = 0; k < NHY; ++k) {
+        int q = t + BLOCK * k;
+        const bool ok = q < nhy;
+        if (!ok) q = nhy - 1;
+        int r = fdiv(q, g.fnx);
+        const int x = q - r * nx;
+        int yy, zz;  // row in Y
+        if (D == 3 && r < 2 * ty) {
+            zz = r < ty ? 0 : tz + 1;
+            yy = 1 + (r < ty ? r : r - ty);
+        } else {
+            if (D == 3) r -= 2 * ty;
+            zz = HZ + (r >> 1);
+            yy = (r & 1) ? ty + 1 : 0;
+        }
+        hyi[k] = ok ? PX + x + nx * (yy + YY * zz) : sink;
+        hyx[k] = x + nx * ((yy + 1) + XY * (zz + HZ));
+        hys[k] = x + nx * (wrap1(y0 - 1 + yy, nx) + (D == 3 ? nx * wrap1(z0 - 1 + zz, nx) : 0));
+        hup[k] = x + 1 == nx ? 1 - nx : 1;
+        hdn[k] = x == 0 ? nx - 1 : -1;
+    }
+    // W applied to V around index j (x neighbours at j + up, j + dn; YS rows a
+    // plane).
+    auto wv = [&](const Acc* V, int j, int up, int dn, int YS) {
+        Acc hop = V[j + up] + V[j + dn];
+        hop += V[j + nx] + V[j - nx];
+        if constexpr (D == 3) hop += V[j + nx * YS] + V[j - nx * YS];
+        return V[j] - kappa * hop;
+    };
+
+    typename Op::craw_t pc[NC];
+    typename Op::lraw_t pa[NC], pah[NHY];
+    typename Op::raw_t ph[NHX];
+    auto prefetch = [&](int sl) {
+        const int off = vs * sl;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            pc[k] = op.load_c(cn[k] + off);
+            pa[k] = op.lraw(cn[k] + off);
+        }
+#pragma unroll
+        for (int k = 0; k < NHX; ++k) ph[k] = op.load_h(hxs[k] + off);
+#pragma unroll
+        for (int k = 0; k < NHY; ++k) pah[k] = op.lraw(hys[k] + off);
+    };
+    Acc xs_c[NC], xn_c[NC], an_c[NC], xs_h[NHY], an_h[NHY];
+    Center cs_c[NC], cn_c[NC];
+    auto stage = [&](int sl) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            xn_c[k] = op.val_c(pc[k], cn_c[k]);
+            an_c[k] = op.lval(pa[k], sl);
+            lds[cok[k] ? cxi[k] : sink] = xn_c[k];
+        }
+#pragma unroll
+        for (int k = 0; k < NHX; ++k) lds[hxi[k]] = op.val_h(ph[k]);
+#pragma unroll
+        for (int k = 0; k < NHY; ++k) an_h[k] = op.lval(pah[k], sl);
+    };
+    // y on the staged slice, at the owned and the Y halo positions; x there
+    // becomes the slice before.
+    auto form_y = [&](Acc (&yo)[NC], Acc (&yh)[NHY]) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+            yo[k] = wv(X, cxi[k], cup[k], cdn[k], XY) + an_c[k] * xs_c[k];
+#pragma unroll
+        for (int k = 0; k < NHY; ++k) {
+            yh[k] = wv(X, hyx[k], hup[k], hdn[k], XY) + an_h[k] * xs_h[k];
+            xs_h[k] = X[hyx[k]];
+        }
+    };
+    auto put_y = [&](const Acc (&yo)[NC], const Acc (&yh)[NHY]) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            lds[cok[k] ? PX + cyi[k] : sink] = yo[k];
+            xs_c[k] = xn_c[k];
+            cs_c[k] = cn_c[k];
+        }
+#pragma unroll
+        for (int k = 0; k < NHY; ++k) lds[hyi[k]] = yh[k];
+    };
+
+    // Prologue: x_{s0-1}, slice s0 into X, y_{s0} into Y, slice s0+1 in flight.
+    {
+        const int offm = vs * wrap1(s0 - 1, nt);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) xs_c[k] = op_in(op, cn[k] + offm);
+#pragma unroll
+        for (int k = 0; k < NHY; ++k) xs_h[k] = op_in(op, hys[k] + offm);
+        prefetch(s0);
+        stage(s0);
+        prefetch(wrap1(s0 + 1, nt));
+        __syncthreads();
+        Acc yo[NC], yh[NHY];
+        form_y(yo, yh);
+        put_y(yo, yh);
+        __syncthreads();
+    }
+    for (int r = 0; r < h; ++r) {
+        const int s = s0 + r;
+        stage(wrap1(s + 1, nt));
+        if (r + 1 < h) prefetch(wrap1(s + 2, nt));
+        __syncthreads();
+        Acc yo[NC], yh[NHY];
+        form_y(yo, yh);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const Acc zv = wv(Y, cyi[k], cup[k], cdn[k], YY) + an_c[k] * yo[k];
+            if (cok[k]) op.out(cn[k] + vs * s, zv, xs_c[k], cs_c[k], part);
+        }
+        __syncthreads();
+        put_y(yo, yh);
+    }
+}
+
+template <class Op, int D, int NC, int NHX, int NHY, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_mtm_rows(Geom g, Op op, int tiles_y, int tiles_z,
+                                                    int tc, double* partials) {
+    extern __shared__ __align__(16) char rows_lds[];
+    if (op.skip()) return;
+    if (!op.begin()) return;
+    const int b = xcd_remap(blockIdx.x, gridDim.x);
+    double part[Op::kNP] = {};
+    tile_mtm_rows<Op, D, NC, NHX, NHY, BLOCK>(g, op, tiles_y, tiles_z, tc, b,
+                                              reinterpret_cast<typename Op::acc_t*>(rows_lds),
+                                              part);
+    if constexpr (Op::kReduce) deposit<BLOCK, Op::kNP>(part, partials, b);
+}
+
+// ---------------------------------------------------------------------------
 // Generic two-pass path for any d and any extents: y = M in (pass 1, into a
 // scratch vector), then z = M^T y with the op's epilogue (pass 2).
 

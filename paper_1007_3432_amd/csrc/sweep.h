@@ -1,6 +1,7 @@
 // Host-side planning and launch of one Q = M^T M sweep with a given op.
 #pragma once
 
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -31,7 +32,13 @@ static constexpr D3Shape kD3Shapes[kD3_Count] = {
     {64, 4, 4, 256}, {16, 8, 4, 256}, {32, 8, 8, 512}, {64, 4, 4, 512}, {64, 8, 4, 512},
     {16, 8, 8, 512}, {32, 8, 4, 512}, {32, 4, 4, 512}, {16, 8, 4, 512}, {8, 8, 8, 512}};
 
-enum SweepKind { kSweepD1 = 0, kSweepD3, kSweepGeneric };
+enum SweepKind { kSweepD1 = 0, kSweepD3, kSweepRows, kSweepGeneric };
+
+// Positions a lane of the row tiles handles at most, and lanes of a block.
+struct RowsLevel { int own, halo_x, halo_y; };
+constexpr RowsLevel kRowsLevels[] = {{1, 2, 1}, {1, 3, 2}, {2, 4, 2}, {2, 7, 4}};
+constexpr int kRowsLevelCount = 4, kRowsBlock = 512;
+constexpr int kRowsLdsMax = 64 * 1024;  // two blocks and more per CU
 
 // Pair tiles of the d = 1 sweep (FP64, nx even): TX sites x TT slices.
 enum D1PTile { kD1P_512x2 = 0, kD1P_256x2, kD1P_128x2, kD1P_512x4, kD1P_512x1, kD1P_Count };
@@ -40,11 +47,12 @@ static constexpr D1Shape kD1PShapes[kD1P_Count] = {
 
 struct SweepPlan {
     int kind;      // SweepKind
-    bool fused;    // single pass (kSweepD1 / kSweepD3)
+    bool fused;    // single pass (all but kSweepGeneric)
     bool pair;     // kSweepD1 with the pair tile (variant is a D1PTile)
-    int variant;   // D1Tile, D1PTile or D3Tile
+    int variant;   // D1Tile, D1PTile, D3Tile or level of the row tiles
     int tiles_x;   // d = 1
-    int tiles_y, tiles_z, tc;  // d = 3: tiles and slices per block
+    int tiles_y, tiles_z, tc;  // d = 2, 3: tiles and slices per block
+    int lds;       // row tiles: elements of LDS
     int ntiles;    // tiles of one sweep = deposits of its reductions
     int grid;      // blocks of the sweep kernel (pass 2 when generic)
 };
@@ -114,6 +122,58 @@ inline bool force_generic() {
     return v;
 }
 
+// The row tiles for a geometry (p->kind stays kSweepGeneric when none fits):
+// the cut with the fewest positions gone through per owned site, counting a
+// slice per chunk for its prologue.
+inline void plan_rows(const Geom& g, SweepPlan* p) {
+    double best = 1e30;
+    // Each tile height once: the next count of tiles that makes it smaller.
+    auto next = [&](int t) { return t > 1 ? ceil_div(g.nx, t - 1) : g.nx + 1; };
+    for (int cy = 1, ty = g.nx; cy <= g.nx; cy = next(ty)) {
+        ty = ceil_div(g.nx, cy);
+        if ((long long)ty * g.nx > 2 * kRowsBlock) continue;
+        for (int cz = 1, tz = g.nx; cz <= (g.d == 3 ? g.nx : 1); cz = next(tz)) {
+            tz = g.d == 3 ? ceil_div(g.nx, cz) : 1;
+            const long long rows = (long long)ty * tz;
+            if (rows * g.nx > 2 * kRowsBlock) continue;
+            const int own = g.nx * (int)rows;
+            const int hx = g.nx * (g.d == 3 ? rows_halo_x<3>(ty, tz) : rows_halo_x<2>(ty, tz));
+            const int hy = g.nx * (g.d == 3 ? rows_halo_y<3>(ty, tz) : rows_halo_y<2>(ty, tz));
+            const int lds = g.d == 3 ? rows_lds_elems<3>(g.nx, ty, tz)
+                                     : rows_lds_elems<2>(g.nx, ty, tz);
+            if (8 * lds > kRowsLdsMax) continue;  // FP64 also in the mixed solver
+            // Where the halo is over three times the tile, two passes read less
+            // (d = 3 90^3 x 6 64.0 us against 60.0, 48^3 x 48 42.2 against 76.0).
+            if (hx > 3 * own) continue;
+            const int tiles = cy * cz;
+            // About two blocks per CU, chunks of 2 to 16 slices (256, 768 and
+            // 1024 blocks were up to 40% slower on one lattice or another).
+            const long long tcl = ((long long)g.nt * tiles + env_int("RB",512)-1) / env_int("RB",512);
+            const int tc = (int)(tcl < 2 ? 2 : (tcl > 16 ? 16 : tcl));
+            const int chunks = ceil_div(g.nt, tc);
+            for (int l = 0; l < kRowsLevelCount; ++l) {
+                if (env_int("RL",-1) >= 0 && env_int("RL",-1) != l) continue;
+                const RowsLevel& K = kRowsLevels[l];
+                if (own > K.own * kRowsBlock || hx > K.halo_x * kRowsBlock ||
+                    hy > K.halo_y * kRowsBlock)
+                    continue;
+                // Waves of blocks over the chip, times what a block does.
+                const double turns = std::ceil(tiles * chunks / 512.0);
+                const double cost = turns * (tc + 1) * (3.0 * K.own + K.halo_x + 2.0 * K.halo_y + 2.0);
+                if (cost >= best) continue;
+                best = cost;
+                p->kind = kSweepRows;
+                p->variant = l;
+                p->tiles_y = cy;
+                p->tiles_z = cz;
+                p->tc = tc;
+                p->lds = lds;
+                p->ntiles = p->grid = tiles * chunks;
+            }
+        }
+    }
+}
+
 // f64: the sweep's ops are FP64 throughout, so the pair tile may serve d = 1.
 // solve: the plan of an FP64 solver (CG phase A and the true residual), which
 // may take another d = 3 tile than the bare product.
@@ -179,6 +239,7 @@ inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false) {
             p.grid = p.ntiles;
         }
     }
+    if (p.kind == kSweepGeneric && !force_generic() && g.d > 1) plan_rows(g, &p);
     if (p.kind == kSweepGeneric) p.ntiles = p.grid = ceil_div(g.V, 256);
     p.fused = p.kind != kSweepGeneric;
     return p;
@@ -217,6 +278,25 @@ inline bool d3_unrolled_ok(const Geom& g, const SweepPlan& P) {
 template <class Op>
 constexpr int d3_unrolled_depth() {
     return 2;
+}
+
+template <class Op, int D, int L>
+inline void launch_rows_l(const Geom& g, const SweepPlan& P, const Op& op, double* partials,
+                          hipStream_t st) {
+    constexpr RowsLevel K = kRowsLevels[L];
+    k_mtm_rows<Op, D, K.own, K.halo_x, K.halo_y, kRowsBlock>
+        <<<P.grid, kRowsBlock, (size_t)P.lds * sizeof(typename Op::acc_t), st>>>(
+            g, op, P.tiles_y, P.tiles_z, P.tc, partials);
+}
+template <class Op, int D>
+inline void launch_rows(const Geom& g, const SweepPlan& P, const Op& op, double* partials,
+                        hipStream_t st) {
+    switch (P.variant) {
+        case 0: launch_rows_l<Op, D, 0>(g, P, op, partials, st); break;
+        case 1: launch_rows_l<Op, D, 1>(g, P, op, partials, st); break;
+        case 2: launch_rows_l<Op, D, 2>(g, P, op, partials, st); break;
+        default: launch_rows_l<Op, D, 3>(g, P, op, partials, st); break;
+    }
 }
 
 // One sweep: z = Q in, consumed by op.out().  y: scratch of g.V acc_t
@@ -335,6 +415,11 @@ hub_status launch_q(const Geom& g, const SweepPlan& P, const Op& op,
             default:
                 return set_error(HUB_E_INVALID, "internal: bad d=3 tile variant");
         }
+    } else if (P.kind == kSweepRows) {
+        if ((size_t)P.lds * sizeof(typename Op::acc_t) > kRowsLdsMax)
+            return set_error(HUB_E_INVALID, "internal: row tile does not fit LDS");
+        if (g.d == 2) launch_rows<Op, 2>(g, P, op, partials, st);
+        else launch_rows<Op, 3>(g, P, op, partials, st);
     } else {
         if (!y) return set_error(HUB_E_INVALID, "internal: generic sweep needs scratch");
         const int grid = ceil_div(g.V, 256);
