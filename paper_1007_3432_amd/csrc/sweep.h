@@ -239,7 +239,18 @@ inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false) {
             p.grid = p.ntiles;
         }
     }
-    if (p.kind == kSweepGeneric && !force_generic() && g.d > 1) plan_rows(g, &p);
+    if (p.kind == kSweepGeneric && !force_generic() && g.d > 1) {
+        // The search takes 1 to 3 us, as long as a launch: the last one of
+        // each thread is kept, by the extents that it depends on.
+        struct Last { int d, nx, nt; SweepPlan p; };
+        static thread_local Last last{0, 0, 0, {}};
+        if (last.d != g.d || last.nx != g.nx || last.nt != g.nt) {
+            SweepPlan q = p;
+            plan_rows(g, &q);
+            last = {g.d, g.nx, g.nt, q};
+        }
+        p = last.p;
+    }
     if (p.kind == kSweepGeneric) p.ntiles = p.grid = ceil_div(g.V, 256);
     p.fused = p.kind != kSweepGeneric;
     return p;

@@ -68,3 +68,14 @@ def test_solve_rows(shape, how):
     r = np.linalg.norm(phi - oracle.apply_MtM(olat, A, x)) / np.linalg.norm(phi)
     assert r <= 1.1e-10
     assert hubtest.rel_err(x, x_o) <= 4 * dense.lanczos_condition(al, be) * 1e-10
+
+
+def test_current_stream():
+    """Calls without a stream go to the stream that is current in torch."""
+    import torch
+    assert hub._stream(None) == torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert hub._stream(None) == s.cuda_stream
+        assert hub._stream(None) == hub._current_stream_slow()
+    assert hub._stream(s) == s.cuda_stream and hub._stream(7) == 7
