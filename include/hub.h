@@ -194,8 +194,9 @@ HUB_API hub_status hub_apply_cheb_noalloc(const hub_lattice* lat, const double* 
  * opts->bulk and opts->link must be HUB_F64.  Convergence is decided on
  * |r| <= tol |phi| and confirmed on the FP64 true residual; a failed
  * confirmation restarts from the true residual.  stats->iters counts CG
- * iterations (each costs 2n + 1 applications of Q).  Blocks until done;
- * keeps its workspace and graphs, and returns, as hub_cg_solve. */
+ * iterations (each costs 2n + 1 applications of Q).  Runs resident on the chip
+ * where hub_cg_solve would, and on smaller lattices.  Blocks until done; keeps
+ * its workspace and graphs, and returns, as hub_cg_solve. */
 HUB_API hub_status hub_pcg_solve(const hub_lattice* lat, const double* sigma,
                          const double* phi, double* x, const hub_cg_opts* opts,
                          const hub_cheb_opts* cheb, hub_cg_stats* out,

@@ -479,9 +479,15 @@ hub_status solve(const Geom& g, const double* sigma, const double* phi, double* 
     if (!mixed && !cheb && cg_small_fits(g)) return cg_solve_small(g, sigma, phi, x, o, out, st);
     HUB_TRY(g_ctx.ensure());
     // One whose vectors fit the registers of the chip stays there.
-    if (!mixed && !cheb) {
+    const double cheb_scale =
+        cheb ? (cheb->scale > 0 ? cheb->scale : cheb_default_scale(g)) : 0.0;
+    if (!mixed) {
+        std::vector<ChebFactor> f;
+        if (cheb) f = cheb_factors(cheb->n, cheb->eps, cheb_scale);
+        static_assert(sizeof(ChebFactor) == 24, "c2, c1, c0");
         bool ran = false;
-        const hub_status r = cg_solve_resident(g, sigma, phi, x, o, out, st, &ran);
+        const hub_status r = cg_solve_resident(g, sigma, phi, x, o, (const double*)f.data(),
+                                               (int)f.size(), out, st, &ran);
         if (ran || r != HUB_OK) return r;
     }
     const size_t V = (size_t)g.V;
@@ -504,8 +510,6 @@ hub_status solve(const Geom& g, const double* sigma, const double* phi, double* 
     const size_t o_w = off; off += cheb ? al(8 * V) : 0;
     char* ws = nullptr;
     HUB_TRY(g_ctx.workspace(off, &ws));
-    const double cheb_scale =
-        cheb ? (cheb->scale > 0 ? cheb->scale : cheb_default_scale(g)) : 0.0;
     const SolveKey key = {(uint64_t)g.d, (uint64_t)g.nx, (uint64_t)g.nt, bits_of(g.kappa),
                           bits_of(g.lscale), bits_of(g.b), (uint64_t)o.bulk,
                           (uint64_t)o.link, bits_of(o.tol), (uint64_t)(uint32_t)o.max_iter,

@@ -43,7 +43,7 @@ ResPlan plan_resident(const Geom& g, int max_blocks) {
             const int own = ceil_div(Tz * Tt, G), rim = ceil_div(2 * H * Tt + Tz, G),
                       halo = ceil_div(2 * (Tz + 2 * H) + 4 * H * Tt, G);
             const size_t lds =
-                8 * (GridSum::kLdsDoubles + 1 + (size_t)inner * ((size_t)(Tz + 4 * H) * (Tt + 2) +
+                8 * (GridSum::kLdsDoubles + 2 + (size_t)inner * ((size_t)(Tz + 4 * H) * (Tt + 2) +
                                            (size_t)(Tz + 2 * H) * (Tt + 1)));
             if (lds > kResLdsMax) continue;
             for (int l = 0; l < kResLevelCount; ++l) {
@@ -67,18 +67,21 @@ ResPlan plan_resident(const Geom& g, int max_blocks) {
     return best;
 }
 
-ResKernel res_kernel(const Geom& g, const ResPlan& p) {
+ResKernel res_kernel(const Geom& g, const ResPlan& p, bool pcg) {
     switch (g.d) {
-        case 1: return res_kernel_d1(p.level, p.whole());
-        case 2: return res_kernel_d2(p.level, p.whole());
-        default: return res_kernel_d3(p.level, p.whole());
+        case 1: return res_kernel_d1(p.level, p.whole(), pcg);
+        case 2: return res_kernel_d2(p.level, p.whole(), pcg);
+        default: return res_kernel_d3(p.level, p.whole(), pcg);
     }
 }
 
-// Empty slots, nothing given up, still running.
-__global__ __launch_bounds__(256) void k_res_reset(uint64_t* slots, ResState* st) {
+constexpr int kFlagWords = kMaxResidentBlocks * kSlotStride;
+
+// Empty slots, flags down, nothing given up, still running.
+__global__ __launch_bounds__(256) void k_res_reset(uint64_t* slots, uint64_t* flags, ResState* st) {
     for (int k = blockIdx.x * 256 + threadIdx.x; k < (int)kSlotWords; k += gridDim.x * 256)
         slots[k] = kSlotEmpty;
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < kFlagWords; k += gridDim.x * 256) flags[k] = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st->given_up = 0;
         st->done = kRunning;
@@ -111,7 +114,7 @@ __global__ __launch_bounds__(256) void k_res_recompute_finish(const double* part
     }
 }
 
-// Iterations of one launch: about 5 ms, after which other streams and threads
+// Products with Q of one launch: about 5 ms, after which other streams and threads
 // get the chip; the state goes through memory in between, some 30 us.
 constexpr int kResChunk = 1000;
 
@@ -139,8 +142,10 @@ std::mutex& resident_mutex(int device) {
 }
 
 hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* phi, double* x,
-                             const hub_cg_opts& o, hub_cg_stats* out, hipStream_t st, bool* ran) {
+                             const hub_cg_opts& o, const double* factors, int nf,
+                             hub_cg_stats* out, hipStream_t st, bool* ran) {
     *ran = false;
+    const bool pcg = nf > 0;
     if (!res_enabled()) return HUB_OK;
     int dev = 0, cus = 0, coop = 0;
     HUB_HIP(hipGetDevice(&dev));
@@ -149,15 +154,15 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
     if (!coop) return HUB_OK;
     const ResPlan p = plan_resident(g, std::min(cus, kMaxResidentBlocks));
     if (p.level < 0) return HUB_OK;
-    const ResKernel kern = res_kernel(g, p);
+    const ResKernel kern = res_kernel(g, p, pcg);
     HUB_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)kResLdsMax));
 
     auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
     const size_t vb = al(8 * (size_t)g.V);
-    const size_t sb = al(8 * kSlotWords);
+    const size_t sb = al(8 * (kSlotWords + kFlagWords)), fb = al(24 * (size_t)nf);
     char* ws = nullptr;
-    hub_status r = solver_workspace(6 * vb + sb + 256, &ws);
+    hub_status r = solver_workspace(6 * vb + sb + 256 + fb, &ws);
     if (r != HUB_OK) return r;
     SolverHost host;
     r = solver_host(&host);
@@ -174,12 +179,19 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
     a.S = (double*)(ws + 3 * vb);
     a.W = (double*)(ws + 4 * vb);  // two vectors
     a.slots = (uint64_t*)(ws + 6 * vb);
+    a.flags = a.slots + kSlotWords;
     a.st = (ResState*)(ws + 6 * vb + sb);
+    a.f = (double*)(ws + 6 * vb + sb + 256);
+    a.nf = nf;
+    if (pcg) {
+        a.S = a.P;  // no s; the recompute's r.s is not used
+        HUB_HIP(hipMemcpyAsync((void*)a.f, factors, 24 * (size_t)nf, hipMemcpyHostToDevice, st));
+    }
     a.phi = phi;
     a.x = x;
     a.tol2 = o.tol * o.tol;
     a.max_iter = o.max_iter;
-    a.iters = kResChunk;
+    a.iters = std::max(2, kResChunk / (2 * nf + 1));
     a.mode = kResFirst;
     a.limit = res_read_limit();
     static_assert(sizeof(ResState) <= sizeof(CGScalars), "snapshot buffer");
@@ -211,7 +223,7 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
     while (done == kRunning) {
         {
             std::lock_guard<std::mutex> lk(resident_mutex(dev));
-            k_res_reset<<<8, 256, 0, st>>>(a.slots, a.st);
+            k_res_reset<<<8, 256, 0, st>>>(a.slots, a.flags, a.st);
             void* args[] = {&a};
             const hipError_t e = hipLaunchCooperativeKernel(
                 (const void*)kern, dim3(p.blocks()), dim3(p.threads), args, (unsigned)p.lds, st);

@@ -2,5 +2,7 @@
 #include "cgres.h"
 
 namespace hub {
-ResKernel res_kernel_d3(int level, bool whole) { return res_kernel_d<3>(level, whole); }
+ResKernel res_kernel_d3(int level, bool whole, bool pcg) {
+    return res_kernel_d<3>(level, whole, pcg);
+}
 }  // namespace hub

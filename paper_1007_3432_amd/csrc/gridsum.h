@@ -12,8 +12,8 @@
 // Stores and loads of slots and of handed-over data are agent-scope relaxed
 // atomics: they go through to, and come from, the memory that all eight L2s
 // share, so no cache has to be written back or invalidated (a release fence
-// at every block costs tens of microseconds on this chip).  Order comes from
-// waiting for the stores' acknowledgement before the deposit.  Measured with
+// at every block costs tens of microseconds on this chip).  Order, where it
+// is needed, comes from waiting for the stores' acknowledgement.  Measured with
 // slots 64 bytes apart: 1.8 us a sum over 16 blocks, 2.0 us over 64, 2.5 us
 // over 256; 8 bytes apart 3.4 us over 256, whose deposits then share lines.
 //

@@ -72,11 +72,13 @@ struct SolverHost {
 };
 hub_status solver_host(SolverHost* out);
 
-// FP64 CG resident on the chip (cgres.hip).  *ran = false, and nothing solved,
+// FP64 CG resident on the chip (cgres.hip), preconditioned by nf quadratic
+// factors (c2, c1, c0 each) where nf > 0.  *ran = false, and nothing solved,
 // when the lattice or the device does not allow it or a wait between blocks
 // was given up; x and the workspace may have been written then.
 hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* phi, double* x,
-                             const hub_cg_opts& o, hub_cg_stats* out, hipStream_t st, bool* ran);
+                             const hub_cg_opts& o, const double* factors, int nf,
+                             hub_cg_stats* out, hipStream_t st, bool* ran);
 // Held while a kernel whose blocks wait for each other runs on the device.
 std::mutex& resident_mutex(int device);
 

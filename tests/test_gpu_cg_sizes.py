@@ -24,7 +24,7 @@ def _lib():
     oracle.set_threads(16)
 
 
-def check(shape):
+def check(shape, cheb=None):
     olat, lat = oracle.Lattice(*shape), hub.lattice(*shape)
     hubtest.log_case(f"cg sizes {shape}")
     sigma, eta = inputs.sigma_eta(*shape, seed=11)
@@ -33,13 +33,18 @@ def check(shape):
     x_o, res, (al, be) = oracle.cg(olat, A, phi, tol=TOL, record=True)
     assert res.converged
     x_d = hubtest.empty(lat.volume, hub.F64)
-    st = hub.hub_cg_solve(lat, hubtest.to_dev(sigma), hubtest.to_dev(phi), x_d, hub.cg_opts(hub.F64))
+    args = (lat, hubtest.to_dev(sigma), hubtest.to_dev(phi), x_d, hub.cg_opts(hub.F64))
+    st = hub.hub_pcg_solve(*args, cheb) if cheb else hub.hub_cg_solve(*args)
     x = x_d.cpu().numpy()
     assert st["status"] == "HUB_OK"
     r = np.linalg.norm(phi - oracle.apply_MtM(olat, A, x)) / np.linalg.norm(phi)
     assert r <= 1.1 * TOL
     assert hubtest.rel_err(x, x_o) <= 4 * dense.lanczos_condition(al, be) * TOL
-    assert abs(st["iters"] - res.iters) <= 0.03 * res.iters + 3
+    if cheb:
+        res = oracle.pcg(olat, A, phi, cheb.n, cheb.eps, tol=TOL)[1]
+        assert abs(st["iters"] - res.iters) <= max(2, 0.05 * res.iters)
+    else:
+        assert abs(st["iters"] - res.iters) <= 0.03 * res.iters + 3
 
 
 @pytest.mark.parametrize("shape", [
@@ -63,11 +68,21 @@ def test_resident(shape):
     check(shape)
 
 
+# One factor and several; lattices below what plain CG keeps in one workgroup.
+@pytest.mark.parametrize("n", [1, 4])
+@pytest.mark.parametrize("shape", [
+    (1, 2, 2), (1, 16, 9), (1, 300, 37), (1, 700, 90), (2, 3, 4), (2, 21, 40), (2, 47, 11), (3, 2, 2),
+    (3, 6, 21), (3, 9, 17), (3, 16, 12), (3, 20, 3)], ids=lambda s: "d%d_%dx%d" % s)
+def test_resident_preconditioned(shape, n):
+    check(shape, hub.cheb_opts(n, 0.01))
+
+
 def test_resident_wait_given_up(monkeypatch):
     """With a single read allowed, blocks give up the first wait for each
     other: the solve ends and is done by the multi-kernel solver."""
     monkeypatch.setenv("HUB_CG_RESIDENT_READS", "1")
     check((1, 256, 32))
+    check((1, 256, 32), hub.cheb_opts(3, 0.01))
 
 
 def test_resident_threads():
