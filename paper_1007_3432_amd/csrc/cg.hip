@@ -74,9 +74,6 @@ __global__ __launch_bounds__(256) void k_phaseB(const CGScalars* sc, Vec* __rest
     deposit<256, 1>(part, partials, blockIdx.x);
 }
 
-// Phase B with the phase-A reduction taken in: every block adds the n_pq
-// p.q deposits (the order of reduce_deposits<256, 1>), sets alpha = rho/p.q,
-// then r -= alpha q and r.r deposits.  Block 0 writes the state to sc_out.
 template <class Vec>
 __global__ __launch_bounds__(256) void k_phaseB_fused(const CGScalars* __restrict__ sc_in,
                                                       CGScalars* __restrict__ sc_out,
@@ -84,51 +81,7 @@ __global__ __launch_bounds__(256) void k_phaseB_fused(const CGScalars* __restric
                                                       int n_pq, Vec* __restrict__ r,
                                                       const Vec* __restrict__ q, int V,
                                                       double* dep_rr) {
-    if (sc_in->done != kRunning) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) *sc_out = *sc_in;
-        return;
-    }
-    // The loads of r and q do not depend on alpha: issue them before the
-    // reduction (a barrier does not wait for outstanding global loads).
-    const int base = lane_base(blockIdx.x), cnt = lane_count(base, V);
-    Vec rv[8], qv[8];
-    if (cnt == 8) {
-        ld8(r + base, rv);
-        ld8(q + base, qv);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            rv[k] = k < cnt ? r[base + eoff(k)] : (Vec)0;
-            qv[k] = k < cnt ? q[base + eoff(k)] : (Vec)0;
-        }
-    }
-    const double pq = reduce_deposits_canon(dep_pq, n_pq);
-    CGScalars s = *sc_in;
-    s.pq = pq;
-    s.gamma = 1.0;
-    if (!(pq > 0.0) || !isfinite(pq)) {
-        s.done = kDoneBreakdown;
-        s.alpha = 0.0;  // alpha_prev was applied by phase A
-    } else {
-        s.alpha = s.rho / pq;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *sc_out = s;
-    if (s.done != kRunning) return;
-    const Vec alpha = (Vec)s.alpha;
-    double part[1] = {0.0};
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        rv[k] = rv[k] - alpha * qv[k];
-        part[0] += (double)rv[k] * (double)rv[k];
-    }
-    if (cnt == 8) {
-        st8(r + base, rv);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (k < cnt) r[base + eoff(k)] = rv[k];
-    }
-    deposit<256, 1>(part, dep_rr, blockIdx.x);
+    phaseB_fused<Vec>(sc_in, sc_out, dep_pq, n_pq, r, q, V, dep_rr, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_phaseB_finish(CGScalars* sc, const double* partials,
@@ -139,19 +92,10 @@ __global__ __launch_bounds__(256) void k_phaseB_finish(CGScalars* sc, const doub
     if (threadIdx.x == 0) finish_phaseB(sc, tot[0]);
 }
 
-// As k_phaseB_finish, reading the state from sc_in and writing it to sc_out.
-// The sum does not depend on the state, so its loads go out first, beside
-// the load of the state; a finished solve's state is only copied.
 __global__ __launch_bounds__(256) void k_phaseB_finish_to(const CGScalars* __restrict__ sc_in,
                                                           CGScalars* __restrict__ sc_out,
                                                           const double* partials, int n) {
-    double tot[1];
-    reduce_deposits<256, 1>(partials, n, tot);
-    if (threadIdx.x == 0) {
-        CGScalars s = *sc_in;
-        if (s.done == kRunning) finish_phaseB(&s, tot[0]);
-        *sc_out = s;
-    }
+    phaseB_finish_to(sc_in, sc_out, partials, n);
 }
 
 __global__ __launch_bounds__(256) void k_pcg_phaseB_finish(CGScalars* sc,

@@ -231,4 +231,77 @@ __device__ __forceinline__ void tile_fold(double* __restrict__ x, float* __restr
     }
 }
 
+// Phase B with the phase-A reduction taken in: every block adds the n_pq
+// p.q deposits (the order of reduce_deposits<256, 1>), sets alpha = rho/p.q,
+// then r -= alpha q and r.r deposits.  The block of tile 0 writes the state to
+// sc_out.  Blocks of 256 lanes, one for each of the tiles.
+template <class Vec>
+__device__ __forceinline__ void phaseB_fused(const CGScalars* __restrict__ sc_in,
+                                             CGScalars* __restrict__ sc_out,
+                                             const double* __restrict__ dep_pq, int n_pq,
+                                             Vec* __restrict__ r, const Vec* __restrict__ q,
+                                             int V, double* dep_rr, int tile) {
+    if (sc_in->done != kRunning) {
+        if (tile == 0 && threadIdx.x == 0) *sc_out = *sc_in;
+        return;
+    }
+    // The loads of r and q do not depend on alpha: issue them before the
+    // reduction (a barrier does not wait for outstanding global loads).
+    const int base = lane_base(tile), cnt = lane_count(base, V);
+    Vec rv[8], qv[8];
+    if (cnt == 8) {
+        ld8(r + base, rv);
+        ld8(q + base, qv);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            rv[k] = k < cnt ? r[base + eoff(k)] : (Vec)0;
+            qv[k] = k < cnt ? q[base + eoff(k)] : (Vec)0;
+        }
+    }
+    const double pq = reduce_deposits_canon(dep_pq, n_pq);
+    CGScalars s = *sc_in;
+    s.pq = pq;
+    s.gamma = 1.0;
+    if (!(pq > 0.0) || !isfinite(pq)) {
+        s.done = kDoneBreakdown;
+        s.alpha = 0.0;  // alpha_prev was applied by phase A
+    } else {
+        s.alpha = s.rho / pq;
+    }
+    if (tile == 0 && threadIdx.x == 0) *sc_out = s;
+    if (s.done != kRunning) return;
+    const Vec alpha = (Vec)s.alpha;
+    double part[1] = {0.0};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        rv[k] = rv[k] - alpha * qv[k];
+        part[0] += (double)rv[k] * (double)rv[k];
+    }
+    if (cnt == 8) {
+        st8(r + base, rv);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (k < cnt) r[base + eoff(k)] = rv[k];
+    }
+    deposit<256, 1>(part, dep_rr, tile);
+}
+
+// After phase B, one block of 256 lanes: the r.r deposits, the state read from
+// sc_in and written to sc_out.  The sum does not depend on the state, so its
+// loads go out first, beside the load of the state; a finished solve's state
+// is only copied.
+__device__ __forceinline__ void phaseB_finish_to(const CGScalars* __restrict__ sc_in,
+                                                 CGScalars* __restrict__ sc_out,
+                                                 const double* partials, int n) {
+    double tot[1];
+    reduce_deposits<256, 1>(partials, n, tot);
+    if (threadIdx.x == 0) {
+        CGScalars s = *sc_in;
+        if (s.done == kRunning) finish_phaseB(&s, tot[0]);
+        *sc_out = s;
+    }
+}
+
 }  // namespace hub

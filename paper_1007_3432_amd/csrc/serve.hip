@@ -51,8 +51,10 @@ struct SlotDesc {
     int kind, variant, tiles_x, tiles_y, tiles_z, tc;
     int sweep_tiles, elem_tiles;
     int off_sweep, off_elem;  // first work item of this solve in each phase
-    CGScalars* sc;
+    CGScalars* sc;   // the state; phase B of the batched engine hands it on
+    CGScalars* sc2;  // through this copy (as k_phaseB_fused)
     double* partials;
+    double* dep_rr;  // phase B's deposits in the batched engine
     const double* phi;
     double* x;
     const double* A64;
@@ -334,74 +336,102 @@ __global__ __launch_bounds__(256) void k_serve_epoch(const SlotDesc* __restrict_
 // Batched engine: the same phases as k_serve_epoch, one launch per phase for
 // all in-flight solves, with one-block-per-solve finalize launches in place
 // of grid barriers (kernel boundaries are the cheaper device-wide sync).
+//
+// Eight chains on four lattices took 32 us an iteration: three sweep launches
+// one after the other (27 us in all while all three run), a finalize, phase B
+// and another finalize.  One launch now sweeps all shapes whose tiles need
+// fewer than 100 registers (a solve's own tile code, chosen per block, so with
+// its bits), and phase B adds the sweep's deposits itself, as in hub_cg_solve:
+// 402 -> 324 ms for the eight solves.  Every solve's tiles are spread over the
+// XCDs, each of which takes a run of them (xcd_remap within the solve), and the
+// solves with the longest tiles come first: 277 ms; runs over all solves' tiles
+// together had given some XCDs only long ones.  (Two slices in flight in the
+// d = 3 tile: 285 ms.)
 
-// Sweep kernels of one tile shape over the in-flight solves of that shape
-// (slots[0 .. n), whose off_sweep count within the group).
-template <class Lnk, int KIND, int A, int B, int C>
-__global__ __launch_bounds__(256) void k_serve_A(const SlotDesc* __restrict__ slots, int n) {
-    const int w = xcd_remap(blockIdx.x, gridDim.x);
-    const SlotDesc& S = slots[find_slot(slots, n, w, true)];
-    if (S.sc->done != kRunning) return;
-    const int tile = w - S.off_sweep;
-    store_deposit<1>(serve_tile_A_body<Lnk, KIND, A, B, C>(&S, tile), S.partials, tile);
+// Solve owning work item w, for offs[0 .. n) ascending from 0: a load and a
+// ballot for each 64 solves, where a binary search over the descriptors is a
+// chain of loads in front of everything that a block does.
+__device__ inline int slot_of(const int* __restrict__ offs, int n, int w) {
+    const int lane = threadIdx.x & 63;
+    int before = 0;
+    for (int k = 0; k < n; k += 64) {
+        const int o = offs[min(k + lane, n - 1)];
+        before += (int)__popcll(__ballot(k + lane < n && o <= w));
+    }
+    return __builtin_amdgcn_readfirstlane(before) - 1;
 }
 
+// Phase-A sweep of the solves slots[0 .. n) whose tiles are any but the one
+// of nx = 32.
 template <class Lnk>
-__global__ __launch_bounds__(256) void k_serve_finA(const SlotDesc* __restrict__ slots) {
-    const SlotDesc& S = slots[blockIdx.x];
+__global__ __launch_bounds__(256) void k_serve_A(const SlotDesc* __restrict__ slots,
+                                                 const int* __restrict__ offs, int n) {
+    const int j = slot_of(offs, n, blockIdx.x);
+    const SlotDesc& S = slots[j];
     if (S.sc->done != kRunning) return;
-    double tot[1];
-    reduce_deposits<256, 1>(S.partials, S.sweep_tiles, tot);
-    if (threadIdx.x == 0) slot_phaseA<Lnk>(S).finish(tot);
+    const int tile = xcd_remap(blockIdx.x - offs[j], S.sweep_tiles);
+    Sums2 r;
+    if (S.kind == kSweepD1) {
+        if (S.variant == kD1_256x4) r = serve_tile_A_body<Lnk, kSweepD1, 256, 4, 0>(&S, tile);
+        else if (S.variant == kD1_128x4) r = serve_tile_A_body<Lnk, kSweepD1, 128, 4, 0>(&S, tile);
+        else r = serve_tile_A_body<Lnk, kSweepD1, 64, 4, 0>(&S, tile);
+    } else if (S.variant == kD3_8x8x8) {
+        r = serve_tile_A_body<Lnk, kSweepD3, 8, 8, 8>(&S, tile);
+    } else {
+        r = serve_tile_A_body<Lnk, kSweepD3, 16, 4, 4>(&S, tile);
+    }
+    store_deposit<1>(r, S.partials, tile);
 }
 
-__global__ __launch_bounds__(256) void k_serve_B(const SlotDesc* __restrict__ slots, int n) {
-    const int w = xcd_remap(blockIdx.x, gridDim.x);
-    const SlotDesc& S = slots[find_slot(slots, n, w, false)];
+// The same for nx = 32, whose tile needs more registers.
+template <class Lnk>
+__global__ __launch_bounds__(256) void k_serve_A32(const SlotDesc* __restrict__ slots,
+                                                   const int* __restrict__ offs, int n) {
+    const int j = slot_of(offs, n, blockIdx.x);
+    const SlotDesc& S = slots[j];
     if (S.sc->done != kRunning) return;
-    double part[1] = {0.0};
-    const int tile = w - S.off_elem;
-    tile_phaseB<float>(S.r, S.q, (float)S.sc->alpha, S.g.V, tile, part);
-    deposit<256, 1>(part, S.partials, tile);
+    const int tile = xcd_remap(blockIdx.x - offs[j], S.sweep_tiles);
+    store_deposit<1>(serve_tile_A_body<Lnk, kSweepD3, 32, 8, 4>(&S, tile), S.partials, tile);
+}
+
+// Phase B with the sweep's reduction taken in (k_phaseB_fused).
+__global__ __launch_bounds__(256) void k_serve_B(const SlotDesc* __restrict__ slots,
+                                                 const int* __restrict__ offs, int n) {
+    const int j = slot_of(offs, n, blockIdx.x);
+    const SlotDesc& S = slots[j];
+    phaseB_fused<float>(S.sc, S.sc2, S.partials, S.sweep_tiles, S.r, S.q, S.g.V, S.dep_rr,
+                        xcd_remap(blockIdx.x - offs[j], S.elem_tiles));
 }
 
 __global__ __launch_bounds__(256) void k_serve_finB(const SlotDesc* __restrict__ slots) {
     const SlotDesc& S = slots[blockIdx.x];
-    if (S.sc->done != kRunning) return;
-    double tot[1];
-    reduce_deposits<256, 1>(S.partials, S.elem_tiles, tot);
-    if (threadIdx.x == 0) finish_phaseB(S.sc, tot[0]);
+    phaseB_finish_to(S.sc2, S.sc, S.dep_rr, S.elem_tiles);
 }
 
-__global__ __launch_bounds__(256) void k_serve_fold(const SlotDesc* __restrict__ slots, int n) {
-    const int w = xcd_remap(blockIdx.x, gridDim.x);
-    const SlotDesc& S = slots[find_slot(slots, n, w, false)];
+__global__ __launch_bounds__(256) void k_serve_fold(const SlotDesc* __restrict__ slots,
+                                                    const int* __restrict__ offs, int n) {
+    const int j = slot_of(offs, n, blockIdx.x);
+    const SlotDesc& S = slots[j];
     if (!mode_runs(kModeReliable, S.sc->done)) return;
     tile_fold<float>(S.x, S.xlo, (S.sc->iter & 1) ? S.p1 : S.p0, S.sc->alpha, S.g.V,
-                     w - S.off_elem);
+                     xcd_remap(blockIdx.x - offs[j], S.elem_tiles));
 }
 
+// True-residual sweep of the solves of one tile shape.
 template <int KIND, int A, int B, int C>
-__global__ __launch_bounds__(256) void k_serve_R(const SlotDesc* __restrict__ slots, int n) {
-    const int w = xcd_remap(blockIdx.x, gridDim.x);
-    const SlotDesc& S = slots[find_slot(slots, n, w, true)];
+__global__ __launch_bounds__(256) void k_serve_R(const SlotDesc* __restrict__ slots,
+                                                 const int* __restrict__ offs, int n) {
+    const int j = slot_of(offs, n, blockIdx.x);
+    const SlotDesc& S = slots[j];
     if (!mode_runs(kModeReliable, S.sc->done)) return;
-    const int tile = w - S.off_sweep;
+    const int tile = xcd_remap(blockIdx.x - offs[j], S.sweep_tiles);
     store_deposit<2>(serve_tile_R_body<KIND, A, B, C>(&S, tile), S.partials, tile);
 }
 
-// Launch the phase-A (R = false) or residual (R = true) sweep of one group of
-// solves that share a tile shape.
-template <class Lnk>
-static hipError_t launch_serve_sweep(bool R, int kind, int variant, const SlotDesc* slots, int n,
-                                     int tiles, size_t lds, hipStream_t st) {
-#define HUB_SERVE_CASE(KIND, A, B, C)                                                    \
-    do {                                                                                 \
-        if (R)                                                                           \
-            k_serve_R<KIND, A, B, C><<<tiles, 256, lds, st>>>(slots, n);                  \
-        else                                                                             \
-            k_serve_A<Lnk, KIND, A, B, C><<<tiles, 256, lds, st>>>(slots, n);             \
-    } while (0)
+static hipError_t launch_serve_R(int kind, int variant, const SlotDesc* slots, const int* offs,
+                                 int n, int tiles, size_t lds, hipStream_t st) {
+#define HUB_SERVE_CASE(KIND, A, B, C) \
+    k_serve_R<KIND, A, B, C><<<tiles, 256, lds, st>>>(slots, offs, n)
     if (kind == kSweepD1) {
         switch (variant) {
             case kD1_256x4: HUB_SERVE_CASE(kSweepD1, 256, 4, 0); break;
@@ -536,7 +566,9 @@ struct hub_server {
     std::vector<Slot> slots;
     SlotDesc* desc_d = nullptr;
     SlotDesc* desc_h = nullptr;  // pinned
-    CGScalars* sc_d = nullptr;   // one per slot
+    int* offs_d = nullptr;       // first work items: sweep A, sweep R, element-wise
+    int* offs_h = nullptr;       // pinned
+    CGScalars* sc_d = nullptr;   // one per slot, then the second copies
     CGScalars* sc_h = nullptr;   // pinned mirror
     EpochCtl* ctl_d = nullptr;
     EpochCtl* ctl_h = nullptr;   // pinned
@@ -723,11 +755,17 @@ hub_status run_epoch(hub_server* S) {
     const int n = (int)ks.size();
     if (n == 0) return HUB_OK;
     auto shape_key = [&](int k) { return S->slots[k].P.kind * 64 + S->slots[k].P.variant; };
+    static_assert(kSweepD1 < kSweepD3 && kD3_32x8x4 > kD3_8x8x8 && kD3_32x8x4 > kD3_16x4x4,
+                  "the nx = 32 tile sorts first");
     std::stable_sort(ks.begin(), ks.end(),
-                     [&](int a, int b) { return shape_key(a) < shape_key(b); });
+                     [&](int a, int b) { return shape_key(a) > shape_key(b); });
     struct Group { int first, count, tiles, kind, variant; };
     std::vector<Group> groups;
     int tot_sweep = 0, tot_elem = 0;
+    // Work items of the phase-A launches: all shapes but nx = 32, and that one.
+    struct { int first, count, tiles; size_t lds; } pa[2] = {};
+    const int m = S->opts.max_inflight;
+    int *offA = S->offs_h, *offR = S->offs_h + m, *offE = S->offs_h + 2 * m;
     for (int j = 0; j < n; ++j) {
         Slot& sl = S->slots[ks[j]];
         if (groups.empty() || shape_key(ks[groups.back().first]) != shape_key(ks[j]))
@@ -746,8 +784,19 @@ hub_status run_epoch(hub_server* S) {
         d.elem_tiles = elem_tiles(d.g.V);
         d.off_sweep = gr.tiles;
         d.off_elem = tot_elem;
+        auto& A = pa[sl.P.kind == kSweepD3 && sl.P.variant == kD3_32x8x4 ? 1 : 0];
+        if (A.count == 0) A.first = j;
+        A.count += 1;
+        offA[j] = A.tiles;
+        offR[j] = gr.tiles;
+        offE[j] = tot_elem;
+        A.tiles += d.sweep_tiles;
+        A.lds = std::max(A.lds, 4 * (size_t)serve_lds_elems(sl.P.kind, sl.P.variant));
         d.sc = &S->sc_d[ks[j]];
+        d.sc2 = &S->sc_d[m + ks[j]];
         d.partials = sl.partials;
+        // The sweep deposits one sum a tile in phase A: the second half is free.
+        d.dep_rr = sl.partials + std::max(d.sweep_tiles, d.elem_tiles);
         d.phi = sl.phi;
         d.x = sl.x;
         d.A64 = sl.chain->A64;
@@ -793,29 +842,32 @@ hub_status run_epoch(hub_server* S) {
                                            kServeLdsBytes, S->stream));
     } else {
         const hipStream_t st = S->stream;
-        auto sweeps = [&](bool R) -> hipError_t {
-            for (const Group& gr : groups) {
-                const size_t lds = (R ? 8 : 4) * (size_t)serve_lds_elems(gr.kind, gr.variant);
-                const hipError_t e =
-                    f16 ? launch_serve_sweep<Link16>(R, gr.kind, gr.variant, descp + gr.first,
-                                                     gr.count, gr.tiles, lds, st)
-                        : launch_serve_sweep<Link32>(R, gr.kind, gr.variant, descp + gr.first,
-                                                     gr.count, gr.tiles, lds, st);
-                if (e != hipSuccess) return e;
-            }
-            return hipSuccess;
-        };
+        HUB_HIP(hipMemcpyAsync(S->offs_d, S->offs_h, sizeof(int) * 3 * m, hipMemcpyHostToDevice,
+                               st));
+        const int *oA = S->offs_d, *oR = S->offs_d + m, *oE = S->offs_d + 2 * m;
         for (int it = 0; it < iters; ++it) {
-            HUB_HIP(sweeps(false));
-            if (f16)
-                k_serve_finA<Link16><<<n, 256, 0, st>>>(descp);
-            else
-                k_serve_finA<Link32><<<n, 256, 0, st>>>(descp);
-            k_serve_B<<<tot_elem, 256, 0, st>>>(descp, n);
+            for (int k = 0; k < 2; ++k) {
+                const auto& A = pa[k];
+                if (A.count == 0) continue;
+                const SlotDesc* sl = descp + A.first;
+                const int* of = oA + A.first;
+                if (k == 0 && f16)
+                    k_serve_A<Link16><<<A.tiles, 256, A.lds, st>>>(sl, of, A.count);
+                else if (k == 0)
+                    k_serve_A<Link32><<<A.tiles, 256, A.lds, st>>>(sl, of, A.count);
+                else if (f16)
+                    k_serve_A32<Link16><<<A.tiles, 256, A.lds, st>>>(sl, of, A.count);
+                else
+                    k_serve_A32<Link32><<<A.tiles, 256, A.lds, st>>>(sl, of, A.count);
+            }
+            k_serve_B<<<tot_elem, 256, 0, st>>>(descp, oE, n);
             k_serve_finB<<<n, 256, 0, st>>>(descp);
         }
-        k_serve_fold<<<tot_elem, 256, 0, st>>>(descp, n);
-        HUB_HIP(sweeps(true));
+        k_serve_fold<<<tot_elem, 256, 0, st>>>(descp, oE, n);
+        for (const Group& gr : groups)
+            HUB_HIP(launch_serve_R(gr.kind, gr.variant, descp + gr.first, oR + gr.first, gr.count,
+                                   gr.tiles, 8 * (size_t)serve_lds_elems(gr.kind, gr.variant),
+                                   st));
         k_serve_finR<<<n, 256, 0, st>>>(descp);
         HUB_HIP(hipGetLastError());
     }
@@ -892,6 +944,8 @@ hub_status server_create(const hub_serve_opts* o, hub_server** out) {
     auto fail = [&](hub_status st) {
         if (S->stream) (void)hipStreamDestroy(S->stream);
         if (S->desc_d) (void)hipFree(S->desc_d);
+        if (S->offs_d) (void)hipFree(S->offs_d);
+        if (S->offs_h) (void)hipHostFree(S->offs_h);
         if (S->sc_d) (void)hipFree(S->sc_d);
         if (S->ctl_d) (void)hipFree(S->ctl_d);
         if (S->desc_h) (void)hipHostFree(S->desc_h);
@@ -924,7 +978,9 @@ hub_status server_create(const hub_serve_opts* o, hub_server** out) {
     const int m = o->max_inflight;
     S->slots.resize(m);
     SRV_HIP(hipMalloc((void**)&S->desc_d, sizeof(SlotDesc) * m));
-    SRV_HIP(hipMalloc((void**)&S->sc_d, sizeof(CGScalars) * m));
+    SRV_HIP(hipMalloc((void**)&S->offs_d, sizeof(int) * 3 * m));
+    SRV_HIP(hipHostMalloc((void**)&S->offs_h, sizeof(int) * 3 * m, hipHostMallocDefault));
+    SRV_HIP(hipMalloc((void**)&S->sc_d, sizeof(CGScalars) * 2 * m));
     SRV_HIP(hipMalloc((void**)&S->ctl_d, sizeof(EpochCtl)));
     SRV_HIP(hipHostMalloc((void**)&S->desc_h, sizeof(SlotDesc) * m, hipHostMallocDefault));
     SRV_HIP(hipHostMalloc((void**)&S->sc_h, sizeof(CGScalars) * m, hipHostMallocDefault));
@@ -1049,6 +1105,8 @@ hub_status hub_serve_destroy(hub_server* srv) {
     (void)hipStreamSynchronize(srv->stream);
     (void)hipStreamDestroy(srv->stream);
     (void)hipFree(srv->desc_d);
+    (void)hipFree(srv->offs_d);
+    (void)hipHostFree(srv->offs_h);
     (void)hipFree(srv->sc_d);
     (void)hipFree(srv->ctl_d);
     (void)hipHostFree(srv->desc_h);
