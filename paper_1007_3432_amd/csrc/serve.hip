@@ -342,11 +342,11 @@ __global__ __launch_bounds__(256) void k_serve_epoch(const SlotDesc* __restrict_
 // and another finalize.  One launch now sweeps all shapes whose tiles need
 // fewer than 100 registers (a solve's own tile code, chosen per block, so with
 // its bits), and phase B adds the sweep's deposits itself, as in hub_cg_solve:
-// 402 -> 324 ms for the eight solves.  Every solve's tiles are spread over the
+// 402 -> 324 ms for the eight solves (to 1e-12).  Every solve's tiles are spread over the
 // XCDs, each of which takes a run of them (xcd_remap within the solve), and the
-// solves with the longest tiles come first: 277 ms; runs over all solves' tiles
+// solves with the longest tiles come first: 297 ms; runs over all solves' tiles
 // together had given some XCDs only long ones.  (Two slices in flight in the
-// d = 3 tile: 285 ms.)
+// d = 3 tile: 3% slower.)
 
 // Solve owning work item w, for offs[0 .. n) ascending from 0: a load and a
 // ballot for each 64 solves, where a binary search over the descriptors is a
@@ -537,7 +537,7 @@ size_t chain_bytes(const Geom& g, hub_dtype link) {
 
 size_t slot_bytes(const Geom& g) {
     const size_t V = (size_t)g.V;
-    const SweepPlan P = plan_sweep(g, false);
+    const SweepPlan P = plan_sweep(g, false, true);
     const int e = elem_tiles(g.V);
     const size_t parts = sizeof(double) * kMaxNP * (size_t)std::max(P.ntiles, e);
     return al256(8 * V) * 2 + al256(4 * V) * 5 + al256(parts);
@@ -648,7 +648,7 @@ hub_status start_slot(hub_server* S, int k, Request&& R) {
     SRV_TRY(upload_chain(S, c, sl.req));
     const Geom& g = sl.req.g;
     const size_t V = (size_t)g.V;
-    sl.P = plan_sweep(g, false);
+    sl.P = plan_sweep(g, false, true);
     sl.bytes = slot_bytes(g);
     HUB_HIP(hipMallocAsync((void**)&sl.mem, sl.bytes, S->stream));
     S->resident += sl.bytes;
@@ -1017,7 +1017,7 @@ hub_status hub_serve_submit(hub_server* srv, int32_t chain_id, const hub_lattice
         if (!phi_host) return set_error(HUB_E_INVALID, "phi_host is NULL");
         Geom g;
         SRV_TRY(make_geom(lat, &g));
-        const SweepPlan P = plan_sweep(g, false);
+        const SweepPlan P = plan_sweep(g, false, true);
         if (!serve_supported(P))
             return set_error(HUB_E_INVALID,
                              "serving steps d=1 lattices and d=3 lattices with nx in {8, 16, "

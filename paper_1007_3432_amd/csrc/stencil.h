@@ -150,6 +150,7 @@ struct OpApply {
     static constexpr bool kPair = sizeof(Acc) == 8 && sizeof(Vec) == 8 &&
                                   std::is_same<Lnk, Link64>::value;
     static constexpr bool kMarch = kPair;
+    static constexpr bool kRepeat = true;
     // The input rows of the pair tiles are loaded with the non-temporal hint
     // (d=1 2048x512: 6.83 -> 6.50 us, 8192x1024: 40.8 -> 34.7 us); the
     // links are not (the same hint on them made both slower again).
@@ -851,6 +852,13 @@ struct op_marches : std::false_type {};
 template <class Op>
 struct op_marches<Op, std::void_t<decltype(Op::kMarch)>> : std::bool_constant<Op::kMarch> {};
 
+// Whether an op's output at a site may be written twice, by two blocks at once
+// (kRepeat, default false): no reduction, and nothing it reads is written.
+template <class Op, class = void>
+struct op_repeats : std::false_type {};
+template <class Op>
+struct op_repeats<Op, std::void_t<decltype(Op::kRepeat)>> : std::bool_constant<Op::kRepeat> {};
+
 // ---------------------------------------------------------------------------
 // Fused Q = M^T M sweep for d = 3, nx = NX.
 //
@@ -883,10 +891,11 @@ constexpr int d3_lds_elems() {
 
 // One tile b of the sweep (block of BLOCK lanes); adds this lane's share of
 // the op's sums to part.  lds: d3_lds_elems<NX, TY, TZ>() elements.
-// TCU > 0: every block marches exactly TCU slices (the caller guarantees
-// tc == TCU and nt % TCU == 0), and the march is unrolled completely, so
-// that no register holding a load in flight has to be copied where the loop
-// would close.
+// TCU > 0: every block marches exactly TCU slices (the caller guarantees nt >=
+// TCU; the last chunk starts early and repeats slices of the one before it, so
+// the op must not mind a site's output written twice), and the march is
+// unrolled completely, so that no register holding a load in flight has to be
+// copied where the loop would close.
 template <class Op, int NX, int TY, int TZ, int BLOCK, int PD = 1, int TCU = 0>
 __device__ __forceinline__ void tile_mtm_d3(const Geom& g, const Op& op, int tiles_y,
                                             int tiles_z, int tc, int b,
@@ -904,8 +913,11 @@ __device__ __forceinline__ void tile_mtm_d3(const Geom& g, const Op& op, int til
     static_assert((NX & (NX - 1)) == 0, "NX must be a power of two");
     static_assert(PZ % BLOCK == 0, "tile must be whole multiples of the block");
     constexpr int NC = PZ / BLOCK;
-    // Halo rows (y, z pairs outside the tile) of the X and Y stages.
-    constexpr int HRX = XY * XZ - TY * TZ, HRY = YY * YZ - TY * TZ;
+    // Halo rows of the X and Y stages: the (y, z) pairs outside the tile that
+    // the stencils reach, at distance 2 and 1, without the corners (which, loaded
+    // and computed as well, cost a lane up to a position of each: FP64 64^3 x 32
+    // 64.4 -> 52.1 us, FP32 32^3 x 256 36.0 -> 28.5, 16^3 x 160 6.2 -> 5.5).
+    constexpr int HRX = 4 * TY + 4 * TZ + 4, HRY = 2 * TY + 2 * TZ;
     constexpr int NHX = (NX * HRX + BLOCK - 1) / BLOCK, NHY = (NX * HRY + BLOCK - 1) / BLOCK;
     Acc* X = lds;
     Acc* Y = lds + PX;
@@ -915,7 +927,8 @@ __device__ __forceinline__ void tile_mtm_d3(const Geom& g, const Op& op, int til
     b /= tiles_y;
     const int iz = b % tiles_z;
     const int ch = b / tiles_z;
-    const int y0 = iy * TY, z0 = iz * TZ, s0 = ch * tc;
+    const int y0 = iy * TY, z0 = iz * TZ;
+    const int s0 = TCU > 0 ? min(ch * TCU, nt - TCU) : ch * tc;
     const int h = TCU > 0 ? TCU : min(tc, nt - s0);
     const int t = threadIdx.x;
     const Acc kappa = (Acc)g.kappa;
@@ -941,18 +954,19 @@ __device__ __forceinline__ void tile_mtm_d3(const Geom& g, const Op& op, int til
         int q = t + BLOCK * k;
         hxo[k] = q < NX * HRX;
         if (!hxo[k]) q = NX * HRX - 1;
-        const int x = q % NX, hr = q / NX;
-        int yx, zx;
-        if (hr < 2 * XY) {
-            zx = hr / XY;
-            yx = hr % XY;
-        } else if (hr < 4 * XY) {
-            zx = TZ + 2 + (hr - 2 * XY) / XY;
-            yx = (hr - 2 * XY) % XY;
-        } else {
-            const int r = hr - 4 * XY, c = r % 4;
-            zx = 2 + r / 4;
-            yx = c < 2 ? c : TY + c;
+        const int x = q % NX;
+        int hr = q / NX, yx, zx;
+        if (hr < 2 * TY) {  // z distance 2: TY rows each
+            zx = hr < TY ? 0 : TZ + 3;
+            yx = 2 + hr % TY;
+        } else if (hr < 4 * TY + 4) {  // z distance 1: TY + 2 rows each
+            hr -= 2 * TY;
+            zx = hr < TY + 2 ? 1 : TZ + 2;
+            yx = 1 + hr % (TY + 2);
+        } else {  // the tile's z: two rows on each side in y
+            hr -= 4 * TY + 4;
+            zx = 2 + hr / 4;
+            yx = hr % 4 < 2 ? hr % 4 : TY + hr % 4;
         }
         hxi[k] = hxo[k] ? x + NX * (yx + XY * zx) : kSink;
         hxs[k] = x + NX * (wrap1(y0 - 2 + yx, NX) + NX * wrap1(z0 - 2 + zx, NX));
@@ -965,15 +979,15 @@ __device__ __forceinline__ void tile_mtm_d3(const Geom& g, const Op& op, int til
         int q = t + BLOCK * k;
         hyo[k] = q < NX * HRY;
         if (!hyo[k]) q = NX * HRY - 1;
-        const int x = q % NX, hr = q / NX;
-        int yy, zz;
-        if (hr < 2 * YY) {
-            zz = hr < YY ? 0 : TZ + 1;
-            yy = hr % YY;
-        } else {
-            const int r = hr - 2 * YY;
-            zz = 1 + r / 2;
-            yy = (r & 1) ? TY + 1 : 0;
+        const int x = q % NX;
+        int hr = q / NX, yy, zz;
+        if (hr < 2 * TY) {  // z distance 1: TY rows each
+            zz = hr < TY ? 0 : TZ + 1;
+            yy = 1 + hr % TY;
+        } else {  // the tile's z: a row on each side in y
+            hr -= 2 * TY;
+            zz = 1 + hr / 2;
+            yy = (hr & 1) ? TY + 1 : 0;
         }
         hyc[k] = x;
         hyi[k] = hyo[k] ? x + NX * (yy + YY * zz) : kSink - PX;

@@ -175,8 +175,8 @@ inline void plan_rows(const Geom& g, SweepPlan* p) {
 }
 
 // f64: the sweep's ops are FP64 throughout, so the pair tile may serve d = 1.
-// solve: the plan of an FP64 solver (CG phase A and the true residual), which
-// may take another d = 3 tile than the bare product.
+// solve: the plan of a solver (CG phase A and the true residual), which may
+// take another d = 3 tile than the bare product.
 inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false) {
     SweepPlan p{};
     p.kind = kSweepGeneric;
@@ -202,21 +202,25 @@ inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false) {
         p.grid = p.ntiles;
     } else if (!force_generic() && g.d == 3) {
         int v = d3_tile_override();
-        if (v >= 0 && (kD3Shapes[v].nx != g.nx || (!f64 && kD3Shapes[v].block != 256))) v = -1;
+        if (v >= 0 && (kD3Shapes[v].nx != g.nx || (!f64 && solve && kD3Shapes[v].block != 256)))
+            v = -1;
         if (v < 0) {
             // Measured on MI355X (bare FP64 and FP32 sweeps on 8^3 x 80,
             // 16^3 x 160, 32^3 x 256, 64^3 x 32): FP64 sweeps run best on
             // 512-lane blocks for nx = 16, 32 (fewer registers per lane than
-            // the 256-lane tiles, whose FP64 CG variant needs 256 VGPRs);
-            // mixed-precision plans stay on 256-lane tiles.
+            // the 256-lane tiles, whose FP64 CG variant needs 256 VGPRs), bare
+            // FP32 ones for nx = 32, 64; mixed-precision solves stay on
+            // 256-lane tiles (their sums are laid out by tile).
             switch (g.nx) {
                 case 8: v = kD3_8x8x8; break;
                 case 16: v = f64 ? kD3_16x8x4_512 : kD3_16x4x4; break;
                 // The FP64 CG iteration on 32^3 x 256 ran faster on 32x8x8
                 // (143.7 vs 150.6 us), the bare FP64 sweep on 32x8x4 (59 vs
                 // 63 us).
-                case 32: v = f64 ? (solve ? kD3_32x8x8_512 : kD3_32x8x4_512) : kD3_32x8x4; break;
-                case 64: v = f64 ? kD3_64x4x4_512 : kD3_64x4x4; break;
+                case 32:
+                    v = !solve ? kD3_32x8x4_512 : (f64 ? kD3_32x8x8_512 : kD3_32x8x4);
+                    break;
+                case 64: v = f64 || !solve ? kD3_64x4x4_512 : kD3_64x4x4; break;
                 default: v = -1;
             }
         }
@@ -259,7 +263,7 @@ inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false) {
 // Doubles of deposit space any reduction over this geometry may need:
 // kMaxNP sums for each tile of the largest grid (sweep or element-wise).
 inline int max_partials(const Geom& g) {
-    const SweepPlan p = plan_sweep(g, false), q = plan_sweep(g, true),
+    const SweepPlan p = plan_sweep(g, false, true), q = plan_sweep(g, true),
                     r = plan_sweep(g, true, true);
     const int e = elem_tiles(g.V);
     int m = p.ntiles > e ? p.ntiles : e;
@@ -277,18 +281,17 @@ constexpr int d3_prefetch_depth() {
     return sizeof(typename Op::acc_t) == 4 ? 2 : 1;
 }
 
-// Slices per block of the completely unrolled d = 3 march, and whether a
-// plan can take it (every block marching exactly that many slices).  Only
-// the bare FP64 product takes it, with two slices in flight: 32^3 x 256
-// 58.0 -> 55.0 us; the FP64 CG phase A would spill registers on it (140 ->
-// 198 us per iteration), the mixed one gains nothing.
+// Slices per block of the completely unrolled d = 3 march, with two slices in
+// flight.  Only the bare products take it, on 512-lane tiles, from the plans
+// whose blocks march the most slices: FP64 32^3 x 256 58.0 -> 54 us, FP32
+// 32^3 x 256 28.5 -> 26.7, 64^3 x 32 29.2 -> 26.8.  The FP64 CG phase A would
+// spill registers on it (140 -> 198 us per iteration), the mixed one gains
+// nothing.  (17 slices, so that chunks do not start at multiples of 4 MiB: 51.4
+// us on the first, but 56.0 for 52.5 on FP64 64^3 x 32 and 26.4 for 25.1 on
+// 32^3 x 128.)
 constexpr int kD3Unroll = 16;
 inline bool d3_unrolled_ok(const Geom& g, const SweepPlan& P) {
-    return P.tc == kD3Unroll && g.nt % kD3Unroll == 0;
-}
-template <class Op>
-constexpr int d3_unrolled_depth() {
-    return 2;
+    return P.tc == 16 && g.nt >= kD3Unroll;
 }
 
 template <class Op, int D, int L>
@@ -397,10 +400,11 @@ hub_status launch_q(const Geom& g, const SweepPlan& P, const Op& op,
         switch (P.variant) {
 #define HUB_D3_CASE(K, NX, TY, TZ, B)                                                    \
     case K:                                                                              \
-        if constexpr (NX >= 32 && op_marches<Op>::value) {                               \
+        if constexpr (NX >= 32 && B == 512 && op_repeats<Op>::value) {                   \
             if (d3_unrolled_ok(g, P)) {                                                  \
-                k_mtm_d3<Op, NX, TY, TZ, B, d3_unrolled_depth<Op>(), kD3Unroll>            \
-                    <<<P.grid, B, 0, st>>>(g, op, P.tiles_y, P.tiles_z, P.tc, partials);  \
+                const int grid = P.tiles_y * P.tiles_z * ceil_div(g.nt, kD3Unroll);       \
+                k_mtm_d3<Op, NX, TY, TZ, B, 2, kD3Unroll><<<grid, B, 0, st>>>(            \
+                    g, op, P.tiles_y, P.tiles_z, kD3Unroll, partials);                    \
                 break;                                                                   \
             }                                                                            \
         }                                                                                \

@@ -79,3 +79,10 @@ def test_current_stream():
         assert hub._stream(None) == s.cuda_stream
         assert hub._stream(None) == hub._current_stream_slow()
     assert hub._stream(s) == s.cuda_stream and hub._stream(7) == 7
+
+
+# The unrolled march of the d = 3 tiles (nx = 32, 64): a last chunk that starts
+# early and repeats slices, and the fewest slices that take it.
+@pytest.mark.parametrize("shape", [(3, 32, 125), (3, 32, 131), (3, 64, 17)], ids=lambda s: "d%d_%dx%d" % s)
+def test_mtm_unrolled(shape):
+    test_mtm_rows(shape)
