@@ -13,6 +13,7 @@
 
 #include "cgtiles.h"
 #include "internal.h"
+#include "stencil.h"
 
 namespace hub {
 
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(256) void k_force(Geom g, double* __restrict__ sigm
     const double y = x[ip] - g.kappa * hop + sg * (1.0 + g.b * sn) * xi;
     const double F = -2.0 * y * (sg * g.b * cs) * xi;
     if constexpr (MODE == kForceOut) {
-        out[i] = F;
+        __builtin_nontemporal_store(F, out + i);
     } else {
         const double p = out[i] - c * F;
         out[i] = p;
@@ -65,7 +66,9 @@ __global__ __launch_bounds__(256) void k_force(Geom g, double* __restrict__ sigm
 }
 
 // The same force for even nx, two x-adjacent sites per lane (16-byte loads
-// and stores; the x neighbours of the pair are its own two values and one
+// and stores, non-temporal for the force and for a sigma that is not written
+// back, as in k_apply_M2: d = 1 2048 x 512 7.3 -> 6.4 us, d = 3 32^3 x 256 52.5
+// -> 42.3, streamed from HBM; the x neighbours of the pair are its own two values and one
 // more site on each side).  Each site's arithmetic is that of k_force, in
 // the same order.
 template <int MODE, int D>
@@ -103,7 +106,14 @@ __global__ __launch_bounds__(256) void k_force2(Geom g, double* __restrict__ sig
         rest = q;
     }
     const double sg = sp == 0 ? g.lscale : -g.lscale;
-    const double2 sv = ld2v(sigma + i), xi = ld2v(x + i);
+    const double2 xi = ld2v(x + i);
+    double2 sv;
+    if constexpr (MODE == kKickDrift) {
+        sv = ld2v(sigma + i);
+    } else {
+        const D2 w = ld2_nt(sigma + i);
+        sv = make_double2(w.a, w.b);
+    }
     double sn_a, cs_a, sn_b, cs_b;
     sincos(sv.x, &sn_a, &cs_a);
     sincos(sv.y, &sn_b, &cs_b);
@@ -112,7 +122,7 @@ __global__ __launch_bounds__(256) void k_force2(Geom g, double* __restrict__ sig
     const double F_a = -2.0 * y_a * (sg * g.b * cs_a) * xi.x;
     const double F_b = -2.0 * y_b * (sg * g.b * cs_b) * xi.y;
     if constexpr (MODE == kForceOut) {
-        *reinterpret_cast<double2*>(out + i) = make_double2(F_a, F_b);
+        st2_nt(out + i, F_a, F_b);
     } else {
         const double2 po = ld2v(out + i);
         const double p_a = po.x - c * F_a, p_b = po.y - c * F_b;
