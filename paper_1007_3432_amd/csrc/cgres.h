@@ -19,12 +19,13 @@
 // keeping p; the next p.Qp is then r.w + 2 beta r.s + beta^2 (p.Qp before), as
 // r has lost its exact orthogonality to the step before.
 //
-// What bounds an iteration is the grid sum (2 to 2.5 us), the halo read after
+// What bounds an iteration is the grid sum (1.8 to 2.5 us), the halo read after
 // it and the LDS traffic of the stencils, where it was three kernels and 80
-// bytes a site of memory traffic.  Before and now, us an iteration: d = 1 256 x 128 9.4 and 3.0, 4096 x 128 15.2 and 4.3, 2048
-// x 512 20.5 and 4.9; d = 2 33 x 60 11.9 and 3.4; d = 3 8^3 x 80 12.1 and 3.2,
-// 16^3 x 128 17.2 and 5.8.  (Hestenes and Stiefel's arrangement, with two grid
-// sums an iteration, took 4.5, 5.7, 7.0, 5.3, 4.8 and 11.0.)
+// bytes a site of memory traffic.  Before and now, us an iteration: d = 1
+// 256 x 128 9.4 and 2.9, 4096 x 128 15.2 and 4.2, 2048 x 512 20.5 and 4.9; d = 2
+// 33 x 60 11.9 and 3.3; d = 3 8^3 x 80 12.1 and 3.2, 16^3 x 128 17.2 and 5.7.
+// (Hestenes and Stiefel's arrangement, with two grid sums an iteration, took
+// 4.5, 5.7, 7.0, 5.3, 4.8 and 11.0.)
 #pragma once
 
 #include <utility>
