@@ -155,23 +155,6 @@ __device__ __forceinline__ void tile_phaseB(Vec* __restrict__ r, const Vec* __re
     }
 }
 
-// After r.r: rho, beta, iteration count; ask for a true-residual recompute
-// when rho meets tol or has dropped by delta^2 since the last one.
-__device__ __forceinline__ void finish_phaseB(CGScalars* sc, double total) {
-    if (!isfinite(total)) {
-        sc->done = kDoneBreakdown;
-        return;
-    }
-    sc->rho_prev = sc->rho;
-    sc->rho = total;
-    sc->beta = total / sc->rho_prev;
-    sc->iter += 1;
-    if (total <= sc->tol2phi2 || total < sc->delta2 * sc->rho_ru)
-        sc->done = kDoneIterConverged;
-    else if (sc->iter >= sc->max_iter)
-        sc->done = kDoneMaxIter;
-}
-
 // Preconditioned CG after r.r: iteration count and convergence on |r|^2
 // (rho, beta belong to r.z and are set after the preconditioner).
 __device__ __forceinline__ void finish_pcg_phaseB(CGScalars* sc, double total) {
@@ -241,12 +224,12 @@ __device__ __forceinline__ void phaseB_fused(const CGScalars* __restrict__ sc_in
                                              const double* __restrict__ dep_pq, int n_pq,
                                              Vec* __restrict__ r, const Vec* __restrict__ q,
                                              int V, double* dep_rr, int tile) {
-    if (sc_in->done != kRunning) {
-        if (tile == 0 && threadIdx.x == 0) *sc_out = *sc_in;
-        return;
-    }
-    // The loads of r and q do not depend on alpha: issue them before the
-    // reduction (a barrier does not wait for outstanding global loads).
+    // One latency for all of it: r, q and the state do not depend on the sum.
+    const bool writes = tile == 0 && threadIdx.x < kStateWords;
+    uint64_t w = 0;
+    if (writes) w = reinterpret_cast<const uint64_t*>(sc_in)[threadIdx.x];
+    const double rho = sc_in->rho;
+    const int was = sc_in->done, updates = sc_in->reliable_updates;
     const int base = lane_base(tile), cnt = lane_count(base, V);
     Vec rv[8], qv[8];
     if (cnt == 8) {
@@ -260,18 +243,17 @@ __device__ __forceinline__ void phaseB_fused(const CGScalars* __restrict__ sc_in
         }
     }
     const double pq = reduce_deposits_canon(dep_pq, n_pq);
-    CGScalars s = *sc_in;
-    s.pq = pq;
-    s.gamma = 1.0;
-    if (!(pq > 0.0) || !isfinite(pq)) {
-        s.done = kDoneBreakdown;
-        s.alpha = 0.0;  // alpha_prev was applied by phase A
-    } else {
-        s.alpha = s.rho / pq;
+    const bool broke = !(pq > 0.0) || !isfinite(pq);
+    const double alpha_d = broke ? 0.0 : rho / pq;  // alpha_prev was applied by phase A
+    if (was == kRunning) {
+        put_word(w, offsetof(CGScalars, pq), pq);
+        put_word(w, offsetof(CGScalars, gamma), 1.0);
+        put_word(w, offsetof(CGScalars, alpha), alpha_d);
+        put_word(w, offsetof(CGScalars, done), broke ? kDoneBreakdown : kRunning, updates);
     }
-    if (tile == 0 && threadIdx.x == 0) *sc_out = s;
-    if (s.done != kRunning) return;
-    const Vec alpha = (Vec)s.alpha;
+    if (writes) reinterpret_cast<uint64_t*>(sc_out)[threadIdx.x] = w;
+    if (was != kRunning || broke) return;
+    const Vec alpha = (Vec)alpha_d;
     double part[1] = {0.0};
 #pragma unroll
     for (int k = 0; k < 8; ++k) {

@@ -231,6 +231,106 @@ __device__ inline double reduce_deposits_canon(const double* partials, int n) {
     return tot;
 }
 
+// After r.r: rho, beta, iteration count; ask for a true-residual recompute
+// when rho meets tol or has dropped by delta^2 since the last one.
+__device__ __forceinline__ void finish_phaseB(CGScalars* sc, double total) {
+    if (!isfinite(total)) {
+        sc->done = kDoneBreakdown;
+        return;
+    }
+    sc->rho_prev = sc->rho;
+    sc->rho = total;
+    sc->beta = total / sc->rho_prev;
+    sc->iter += 1;
+    if (total <= sc->tol2phi2 || total < sc->delta2 * sc->rho_ru)
+        sc->done = kDoneIterConverged;
+    else if (sc->iter >= sc->max_iter)
+        sc->done = kDoneMaxIter;
+}
+
+// The sum of n <= 256 PER single-value deposits in the order of
+// reduce_deposits<256, 1>, so with its bits, by every wavefront for itself:
+// all loads at once and no barrier, so that nothing else the kernel has to
+// load waits for it.
+template <int PER>
+__device__ __forceinline__ double reduce_deposits_wave(const double* __restrict__ partials,
+                                                       int n) {
+    constexpr int kG = 4;  // wavefronts of the 256-lane block whose order this is
+    const int lane = threadIdx.x & 63;
+    double v[kG * PER];
+#pragma unroll
+    for (int k = 0; k < kG * PER; ++k) v[k] = partials[min(64 * k + lane, n - 1)];
+    double tot = 0.0;
+#pragma unroll
+    for (int k = 0; k < kG; ++k) {
+        double s = 0.0;
+#pragma unroll
+        for (int j = k; j < kG * PER; j += kG) s += 64 * j + lane < n ? v[j] : 0.0;
+        tot += wave_sum(s);
+    }
+    return tot;
+}
+
+// PER for n deposits; 0: too many, a block or a kernel of its own adds them.
+// Measured as the last deposits of FP32 CG iterations, taken into the sweep
+// after them: 240 of them 14.2 -> 12.8 us an iteration, 375 18.0 -> 16.3.
+inline int wave_deposits(int n) { return n <= 256 ? 1 : n <= 512 ? 2 : 0; }
+
+// The solver state as words, one a lane: a block that hands the state on loads
+// its lane's word beside its other loads, puts the new values in and stores it,
+// where a copy by one lane would add a load's latency to the kernel.
+constexpr int kStateWords = sizeof(CGScalars) / 8;
+static_assert(kStateWords <= 64 && offsetof(CGScalars, iter) % 8 == 0 &&
+                  offsetof(CGScalars, max_iter) == offsetof(CGScalars, iter) + 4 &&
+                  offsetof(CGScalars, done) % 8 == 0 &&
+                  offsetof(CGScalars, reliable_updates) == offsetof(CGScalars, done) + 4,
+              "pairs of 32-bit fields that share a word");
+__device__ __forceinline__ void put_word(uint64_t& w, size_t offset, double v) {
+    if (threadIdx.x == offset / 8) w = (uint64_t)__double_as_longlong(v);
+}
+__device__ __forceinline__ void put_word(uint64_t& w, size_t offset, int lo, int hi) {
+    if (threadIdx.x == offset / 8) w = (uint64_t)(uint32_t)hi << 32 | (uint32_t)lo;
+}
+
+// finish_phaseB by every wavefront for itself: the state left in *from and its
+// n r.r deposits give what a sweep has to know of the next state, and the lead
+// block writes that state to *to.
+// A solve that has ended stays as it is.
+struct NextState {
+    double beta;
+    int iter, done;
+};
+template <int PER>
+__device__ __forceinline__ NextState phaseB_take(const CGScalars* __restrict__ from,
+                                                 CGScalars* __restrict__ to,
+                                                 const double* __restrict__ dep_rr, int n,
+                                                 bool lead) {
+    const bool writes = lead && threadIdx.x < kStateWords;
+    uint64_t w = 0;
+    if (writes) w = reinterpret_cast<const uint64_t*>(from)[threadIdx.x];
+    const double rho = from->rho, tol = from->tol2phi2, drop = from->delta2 * from->rho_ru;
+    const int max_iter = from->max_iter, updates = from->reliable_updates;
+    NextState s{from->beta, from->iter, from->done};
+    const double rr = reduce_deposits_wave<PER>(dep_rr, n);
+    if (s.done == kRunning) {
+        if (!isfinite(rr)) {
+            s.done = kDoneBreakdown;
+        } else {
+            s.beta = rr / rho;
+            s.iter += 1;
+            s.done = rr <= tol || rr < drop ? kDoneIterConverged
+                                            : s.iter >= max_iter ? kDoneMaxIter : kRunning;
+            put_word(w, offsetof(CGScalars, rho), rr);
+            put_word(w, offsetof(CGScalars, rho_prev), rho);
+            put_word(w, offsetof(CGScalars, beta), s.beta);
+            put_word(w, offsetof(CGScalars, iter), s.iter, max_iter);
+        }
+        put_word(w, offsetof(CGScalars, done), s.done, updates);
+    }
+    if (writes) reinterpret_cast<uint64_t*>(to)[threadIdx.x] = w;
+    return s;
+}
+
 // Largest number of sums any reduction deposits per tile.
 constexpr int kMaxNP = 2;
 

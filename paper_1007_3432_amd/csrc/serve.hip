@@ -147,9 +147,13 @@ __device__ Link16 slot_link<Link16>(const SlotDesc& S) {
     return l;
 }
 
-template <class Lnk>
-__device__ OpPhaseA<float, float, float, Lnk> slot_phaseA(const SlotDesc& S) {
-    OpPhaseA<float, float, float, Lnk> op{};
+template <class Lnk, int PER = 0>
+using SlotOp = OpPhaseA<float, float, float, Lnk, PER>;
+
+// PER > 0 (batched engine): the sweep finishes the phase B before it.
+template <class Lnk, int PER = 0>
+__device__ SlotOp<Lnk, PER> slot_op(const SlotDesc& S) {
+    SlotOp<Lnk, PER> op{};
     op.sc = S.sc;
     op.r = S.r;
     op.pbuf0 = S.p0;
@@ -157,7 +161,18 @@ __device__ OpPhaseA<float, float, float, Lnk> slot_phaseA(const SlotDesc& S) {
     op.q = S.q;
     op.x = S.xlo;
     op.lk = slot_link<Lnk>(S);
-    (void)op.begin();
+    if constexpr (PER > 0) {
+        op.sc_b = S.sc2;
+        op.dep_rr = S.dep_rr;
+        op.n_rr = S.elem_tiles;
+    }
+    return op;
+}
+
+template <class Lnk>
+__device__ SlotOp<Lnk> slot_phaseA(const SlotDesc& S) {
+    auto op = slot_op<Lnk>(S);
+    (void)op.take(false);
     return op;
 }
 
@@ -179,16 +194,14 @@ struct Sums2 {
 // inlined; the persistent engine runs every shape in one kernel and calls
 // them as functions (serve_tile_A / serve_tile_R), each (op, tile shape)
 // pair register-allocated on its own.
-template <class Lnk, int KIND, int A, int B, int C>
-__device__ __forceinline__ Sums2 serve_tile_A_body(const SlotDesc* S, int tile) {
-    const auto op = slot_phaseA<Lnk>(*S);
+template <int KIND, int A, int B, int C, class Op>
+__device__ __forceinline__ Sums2 serve_tile_A_body(const SlotDesc* S, int tile, const Op& op) {
     double part[1] = {0.0};
     float* lds = reinterpret_cast<float*>(serve_smem);
     if constexpr (KIND == kSweepD1)
-        tile_mtm_d1<decltype(op), A, B>(S->g, op, S->tiles_x, tile, lds, part);
+        tile_mtm_d1<Op, A, B>(S->g, op, S->tiles_x, tile, lds, part);
     else
-        tile_mtm_d3<decltype(op), A, B, C, 256>(S->g, op, S->tiles_y, S->tiles_z, S->tc, tile,
-                                                lds, part);
+        tile_mtm_d3<Op, A, B, C, 256>(S->g, op, S->tiles_y, S->tiles_z, S->tc, tile, lds, part);
     Sums2 r{block_sum<256>(part[0]), 0.0};
     return r;
 }
@@ -211,7 +224,7 @@ __device__ __forceinline__ Sums2 serve_tile_R_body(const SlotDesc* S, int tile) 
 
 template <class Lnk, int KIND, int A, int B, int C>
 __device__ __noinline__ Sums2 serve_tile_A(const SlotDesc* S, int tile) {
-    return serve_tile_A_body<Lnk, KIND, A, B, C>(S, tile);
+    return serve_tile_A_body<KIND, A, B, C>(S, tile, slot_phaseA<Lnk>(*S));
 }
 
 template <int KIND, int A, int B, int C>
@@ -346,7 +359,9 @@ __global__ __launch_bounds__(256) void k_serve_epoch(const SlotDesc* __restrict_
 // XCDs, each of which takes a run of them (xcd_remap within the solve), and the
 // solves with the longest tiles come first: 297 ms; runs over all solves' tiles
 // together had given some XCDs only long ones.  (Two slices in flight in the
-// d = 3 tile: 3% slower.)
+// d = 3 tile: 3% slower.)  The finalize of phase B is taken into the next sweep
+// where no solve has more than 512 deposits (cg.hip), leaving two launches an
+// iteration: 275 -> 258 ms.
 
 // Solve owning work item w, for offs[0 .. n) ascending from 0: a load and a
 // ballot for each 64 solves, where a binary search over the descriptors is a
@@ -363,35 +378,50 @@ __device__ inline int slot_of(const int* __restrict__ offs, int n, int w) {
 
 // Phase-A sweep of the solves slots[0 .. n) whose tiles are any but the one
 // of nx = 32.
-template <class Lnk>
+template <class Lnk, int PER>
 __global__ __launch_bounds__(256) void k_serve_A(const SlotDesc* __restrict__ slots,
                                                  const int* __restrict__ offs, int n) {
     const int j = slot_of(offs, n, blockIdx.x);
     const SlotDesc& S = slots[j];
-    if (S.sc->done != kRunning) return;
+    auto op = slot_op<Lnk, PER>(S);
+    if (!op.take((int)blockIdx.x == offs[j])) return;
     const int tile = xcd_remap(blockIdx.x - offs[j], S.sweep_tiles);
     Sums2 r;
     if (S.kind == kSweepD1) {
-        if (S.variant == kD1_256x4) r = serve_tile_A_body<Lnk, kSweepD1, 256, 4, 0>(&S, tile);
-        else if (S.variant == kD1_128x4) r = serve_tile_A_body<Lnk, kSweepD1, 128, 4, 0>(&S, tile);
-        else r = serve_tile_A_body<Lnk, kSweepD1, 64, 4, 0>(&S, tile);
+        if (S.variant == kD1_256x4) r = serve_tile_A_body<kSweepD1, 256, 4, 0>(&S, tile, op);
+        else if (S.variant == kD1_128x4) r = serve_tile_A_body<kSweepD1, 128, 4, 0>(&S, tile, op);
+        else r = serve_tile_A_body<kSweepD1, 64, 4, 0>(&S, tile, op);
     } else if (S.variant == kD3_8x8x8) {
-        r = serve_tile_A_body<Lnk, kSweepD3, 8, 8, 8>(&S, tile);
+        r = serve_tile_A_body<kSweepD3, 8, 8, 8>(&S, tile, op);
     } else {
-        r = serve_tile_A_body<Lnk, kSweepD3, 16, 4, 4>(&S, tile);
+        r = serve_tile_A_body<kSweepD3, 16, 4, 4>(&S, tile, op);
     }
     store_deposit<1>(r, S.partials, tile);
 }
 
 // The same for nx = 32, whose tile needs more registers.
-template <class Lnk>
+template <class Lnk, int PER>
 __global__ __launch_bounds__(256) void k_serve_A32(const SlotDesc* __restrict__ slots,
                                                    const int* __restrict__ offs, int n) {
     const int j = slot_of(offs, n, blockIdx.x);
     const SlotDesc& S = slots[j];
-    if (S.sc->done != kRunning) return;
+    auto op = slot_op<Lnk, PER>(S);
+    if (!op.take((int)blockIdx.x == offs[j])) return;
     const int tile = xcd_remap(blockIdx.x - offs[j], S.sweep_tiles);
-    store_deposit<1>(serve_tile_A_body<Lnk, kSweepD3, 32, 8, 4>(&S, tile), S.partials, tile);
+    store_deposit<1>(serve_tile_A_body<kSweepD3, 32, 8, 4>(&S, tile, op), S.partials, tile);
+}
+
+using SweepKernel = void (*)(const SlotDesc*, const int*, int);
+template <class Lnk>
+static SweepKernel serve_A_kernel(bool nx32, int per) {
+    if (nx32)
+        return per == 1   ? k_serve_A32<Lnk, 1>
+               : per == 2 ? k_serve_A32<Lnk, 2>
+                          : k_serve_A32<Lnk, 0>;
+    return per == 1 ? k_serve_A<Lnk, 1> : per == 2 ? k_serve_A<Lnk, 2> : k_serve_A<Lnk, 0>;
+}
+static SweepKernel serve_A_kernel(bool nx32, bool f16, int per) {
+    return f16 ? serve_A_kernel<Link16>(nx32, per) : serve_A_kernel<Link32>(nx32, per);
 }
 
 // Phase B with the sweep's reduction taken in (k_phaseB_fused).
@@ -762,6 +792,7 @@ hub_status run_epoch(hub_server* S) {
     struct Group { int first, count, tiles, kind, variant; };
     std::vector<Group> groups;
     int tot_sweep = 0, tot_elem = 0;
+    int most_rr = 0;  // most deposits of a solve in phase B
     // Work items of the phase-A launches: all shapes but nx = 32, and that one.
     struct { int first, count, tiles; size_t lds; } pa[2] = {};
     const int m = S->opts.max_inflight;
@@ -809,6 +840,7 @@ hub_status run_epoch(hub_server* S) {
         gr.count += 1;
         gr.tiles += d.sweep_tiles;
         tot_elem += d.elem_tiles;
+        most_rr = std::max(most_rr, d.elem_tiles);
     }
     HUB_HIP(hipMemcpyAsync(S->desc_d, S->desc_h, sizeof(SlotDesc) * n, hipMemcpyHostToDevice,
                            S->stream));
@@ -845,23 +877,16 @@ hub_status run_epoch(hub_server* S) {
         HUB_HIP(hipMemcpyAsync(S->offs_d, S->offs_h, sizeof(int) * 3 * m, hipMemcpyHostToDevice,
                                st));
         const int *oA = S->offs_d, *oR = S->offs_d + m, *oE = S->offs_d + 2 * m;
+        const int next = wave_deposits(most_rr);
         for (int it = 0; it < iters; ++it) {
             for (int k = 0; k < 2; ++k) {
                 const auto& A = pa[k];
                 if (A.count == 0) continue;
-                const SlotDesc* sl = descp + A.first;
-                const int* of = oA + A.first;
-                if (k == 0 && f16)
-                    k_serve_A<Link16><<<A.tiles, 256, A.lds, st>>>(sl, of, A.count);
-                else if (k == 0)
-                    k_serve_A<Link32><<<A.tiles, 256, A.lds, st>>>(sl, of, A.count);
-                else if (f16)
-                    k_serve_A32<Link16><<<A.tiles, 256, A.lds, st>>>(sl, of, A.count);
-                else
-                    k_serve_A32<Link32><<<A.tiles, 256, A.lds, st>>>(sl, of, A.count);
+                serve_A_kernel(k == 1, f16, it == 0 ? 0 : next)<<<A.tiles, 256, A.lds, st>>>(
+                    descp + A.first, oA + A.first, A.count);
             }
             k_serve_B<<<tot_elem, 256, 0, st>>>(descp, oE, n);
-            k_serve_finB<<<n, 256, 0, st>>>(descp);
+            if (next == 0 || it == iters - 1) k_serve_finB<<<n, 256, 0, st>>>(descp);
         }
         k_serve_fold<<<tot_elem, 256, 0, st>>>(descp, oE, n);
         for (const Group& gr : groups)

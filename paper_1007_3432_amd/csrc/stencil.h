@@ -170,7 +170,7 @@ struct OpApply {
 // p is double-buffered by iteration parity so halo reads never see a p_new.
 // The p.q deposits are added either by a one-block finalize (finish(), which
 // sets alpha) or by the next kernel's blocks themselves.
-template <class Acc, class Vec, class XVec, class Lnk>
+template <class Acc, class Vec, class XVec, class Lnk, int PER = 0>
 struct OpPhaseA {
     using acc_t = Acc;
     struct center_t {
@@ -194,20 +194,36 @@ struct OpPhaseA {
     Vec* q;
     XVec* x;
     Lnk lk;
-    // set by begin()
+    // PER > 0: where the last phase B left its state and its r.r deposits (at
+    // most 256 PER), which this sweep has to finish.  Otherwise *sc is the state.
+    const CGScalars* sc_b;
+    const double* dep_rr;
+    int n_rr;
+    // set by take()
     const Vec* pold;
     Vec* pnew;
     Acc beta, alpha, gamma;
-    __device__ bool skip() const { return sc->done != kRunning; }
-    __device__ bool begin() {
-        const int it = sc->iter;
-        pold = (it & 1) ? pbuf1 : pbuf0;
-        pnew = (it & 1) ? pbuf0 : pbuf1;
-        beta = (Acc)sc->beta;
-        alpha = (Acc)sc->alpha;
-        gamma = (Acc)sc->gamma;
-        return true;
+    // The state this sweep starts from; false when the solve is not running.
+    // With PER every block adds phase B's deposits itself and the lead block
+    // writes the state to *sc, where the next phase B reads it.  All lanes.
+    __device__ bool take(bool lead) {
+        NextState s;
+        if constexpr (PER > 0) {
+            s = phaseB_take<PER>(sc_b, sc, dep_rr, n_rr, lead);
+            alpha = (Acc)sc_b->alpha;
+            gamma = (Acc)sc_b->gamma;
+        } else {
+            s = {sc->beta, sc->iter, sc->done};
+            alpha = (Acc)sc->alpha;
+            gamma = (Acc)sc->gamma;
+        }
+        beta = (Acc)s.beta;
+        pold = (s.iter & 1) ? pbuf1 : pbuf0;
+        pnew = (s.iter & 1) ? pbuf0 : pbuf1;
+        return s.done == kRunning;
     }
+    __device__ bool skip() { return !take(blockIdx.x == 0); }
+    __device__ bool begin() { return true; }
     __device__ raw_t load_h(int i) const { return {r[i], pold[i]}; }
     __device__ Acc val_h(const raw_t& v) const { return gamma * (Acc)v.r + beta * (Acc)v.p; }
     __device__ craw_t load_c(int i) const { return {r[i], pold[i], x[i]}; }
