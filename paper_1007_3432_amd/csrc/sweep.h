@@ -214,11 +214,16 @@ inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false) {
             switch (g.nx) {
                 case 8: v = kD3_8x8x8; break;
                 case 16: v = f64 ? kD3_16x8x4_512 : kD3_16x4x4; break;
-                // The FP64 CG iteration on 32^3 x 256 ran faster on 32x8x8
-                // (143.7 vs 150.6 us), the bare FP64 sweep on 32x8x4 (59 vs
-                // 63 us).
+                // Eight planes of z a tile wherever its blocks fill the chip
+                // (a lane's four sites in z give each other their neighbours):
+                // bare FP64 product, 32x8x4 and 32x8x8, 32^3 x 256 52.0 and
+                // 48.4 us, x 144 35.7 and 26.4, x 32 10.2 and 9.3, x 20 8.3 and
+                // 8.5, x 8 6.4 and 8.1; FP32 x 256 24.5 and 21.5, x 20 6.4 and
+                // 6.6.  (x 128, whose 32x8x4 march is the unrolled one: 23.7
+                // and 24.4, in FP32 17.0 and 14.2.)
                 case 32:
-                    v = !solve ? kD3_32x8x4_512 : (f64 ? kD3_32x8x8_512 : kD3_32x8x4);
+                    if (solve) v = f64 ? kD3_32x8x8_512 : kD3_32x8x4;
+                    else v = g.nt >= 24 ? kD3_32x8x8_512 : kD3_32x8x4_512;
                     break;
                 case 64: v = f64 || !solve ? kD3_64x4x4_512 : kD3_64x4x4; break;
                 default: v = -1;
@@ -283,8 +288,8 @@ constexpr int d3_prefetch_depth() {
 
 // Slices per block of the completely unrolled d = 3 march, with two slices in
 // flight.  Only the bare products take it, on 512-lane tiles, from the plans
-// whose blocks march the most slices: FP64 32^3 x 256 58.0 -> 54 us, FP32
-// 32^3 x 256 28.5 -> 26.7, 64^3 x 32 29.2 -> 26.8.  The FP64 CG phase A would
+// whose blocks march the most slices: on 32x8x4 tiles FP64 32^3 x 256 58.0 -> 54
+// us, FP32 32^3 x 256 28.5 -> 26.7, 64^3 x 32 29.2 -> 26.8.  The FP64 CG phase A would
 // spill registers on it (140 -> 198 us per iteration), the mixed one gains
 // nothing.  (17 slices, so that chunks do not start at multiples of 4 MiB: 51.4
 // us on the first, but 56.0 for 52.5 on FP64 64^3 x 32 and 26.4 for 25.1 on

@@ -86,3 +86,10 @@ def test_current_stream():
 @pytest.mark.parametrize("shape", [(3, 32, 125), (3, 32, 131), (3, 64, 17)], ids=lambda s: "d%d_%dx%d" % s)
 def test_mtm_unrolled(shape):
     test_mtm_rows(shape)
+
+
+@pytest.mark.parametrize("nt", [2, 23, 24, 31, 243])
+def test_nx32_tile_by_slices(nt):
+    """nx = 32 on either side of the number of slices that chooses its tile,
+    and where the larger tile's march is unrolled."""
+    test_mtm_rows((3, 32, nt))
