@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void k_init_finish(CGScalars* sc, const double
     if (threadIdx.x == 0) finish_init(sc, tot[0], tol2, delta2, max_iter);
 }
 
-// r -= alpha q, r.r (deposits; k_phaseB_finish).
+// r -= alpha q, r.r (deposits; k_pcg_phaseB_finish).
 template <class Vec>
 __global__ __launch_bounds__(256) void k_phaseB(const CGScalars* sc, Vec* __restrict__ r,
                                                 const Vec* __restrict__ q, int V,
@@ -88,14 +88,6 @@ __global__ __launch_bounds__(256) void k_phaseB_fused(const CGScalars* __restric
                                                       const Vec* __restrict__ q, int V,
                                                       double* dep_rr) {
     phaseB_fused<Vec>(sc_in, sc_out, dep_pq, n_pq, r, q, V, dep_rr, blockIdx.x);
-}
-
-__global__ __launch_bounds__(256) void k_phaseB_finish(CGScalars* sc, const double* partials,
-                                                       int n) {
-    if (sc->done != kRunning) return;
-    double tot[1];
-    reduce_deposits<256, 1>(partials, n, tot);
-    if (threadIdx.x == 0) finish_phaseB(sc, tot[0]);
 }
 
 __global__ __launch_bounds__(256) void k_phaseB_finish_to(const CGScalars* __restrict__ sc_in,
@@ -304,17 +296,12 @@ struct Solver {
             return HUB_OK;
         }
         for (int k = 0; k < iters; ++k) {
-            if constexpr (sizeof(Vec) == 8) {
-                if (pcg)
-                    HUB_TRY(launch_cheb(g, P, A64, sc, r, z, w, yscratch, partials, cheb.data(),
-                                        (int)cheb.size(), true, st));
-            }
+            if constexpr (sizeof(Vec) == 8)
+                HUB_TRY(launch_cheb(g, P, A64, sc, r, z, w, yscratch, partials, cheb.data(),
+                                    (int)cheb.size(), true, st));
             HUB_TRY(launch_q(g, P, opA, (Vec*)yscratch, partials, st));
             k_phaseB<Vec><<<elem_tiles(g.V), 256, 0, st>>>(sc, r, q, g.V, partials);
-            if (pcg)
-                k_pcg_phaseB_finish<<<1, 256, 0, st>>>(sc, partials, elem_tiles(g.V));
-            else
-                k_phaseB_finish<<<1, 256, 0, st>>>(sc, partials, elem_tiles(g.V));
+            k_pcg_phaseB_finish<<<1, 256, 0, st>>>(sc, partials, elem_tiles(g.V));
         }
         HUB_TRY(fold_and_residual(mixed ? kModeReliable : kModeCheck));
         HUB_HIP(hipMemcpyAsync(snap, sc, sizeof(CGScalars), hipMemcpyDeviceToHost, st));

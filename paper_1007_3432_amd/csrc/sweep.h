@@ -413,8 +413,11 @@ hub_status launch_q(const Geom& g, const SweepPlan& P, const Op& op,
                 break;                                                                   \
             }                                                                            \
         }                                                                                \
-        k_mtm_d3<Op, NX, TY, TZ, B, d3_prefetch_depth<Op>()>                              \
-            <<<P.grid, B, 0, st>>>(g, op, P.tiles_y, P.tiles_z, P.tc, partials);          \
+        if constexpr (B == 256 || sizeof(typename Op::acc_t) == 8 || !Op::kReduce)         \
+            k_mtm_d3<Op, NX, TY, TZ, B, d3_prefetch_depth<Op>()>                          \
+                <<<P.grid, B, 0, st>>>(g, op, P.tiles_y, P.tiles_z, P.tc, partials);      \
+        else                                                                             \
+            return set_error(HUB_E_INVALID, "internal: mixed solves take 256-lane tiles"); \
         break;
             HUB_D3_CASE(kD3_8x8x8, 8, 8, 8, 256)
             HUB_D3_CASE(kD3_16x4x4, 16, 4, 4, 256)
