@@ -190,10 +190,11 @@ struct Sums2 {
 };
 
 // One sweep tile of solve *S.  Returns the block sums (thread 0).  The
-// batched engine launches one kernel per tile shape, with these bodies
-// inlined; the persistent engine runs every shape in one kernel and calls
-// them as functions (serve_tile_A / serve_tile_R), each (op, tile shape)
-// pair register-allocated on its own.
+// batched engine's kernels have these bodies inlined, all shapes but nx = 32 in
+// one for phase A, a kernel for each shape for the residual; the persistent
+// engine runs every shape in one kernel and calls them as functions
+// (serve_tile_A / serve_tile_R), each (op, tile shape) pair register-allocated
+// on its own.
 template <int KIND, int A, int B, int C, class Op>
 __device__ __forceinline__ Sums2 serve_tile_A_body(const SlotDesc* S, int tile, const Op& op) {
     double part[1] = {0.0};
@@ -777,8 +778,9 @@ hub_status finish_slot(hub_server* S, int k) {
 }
 
 hub_status run_epoch(hub_server* S) {
-    // In-flight solves, grouped by tile shape so that each sweep launch runs
-    // one shape: off_sweep counts within the group, off_elem over all.
+    // In-flight solves, grouped by tile shape for the residual sweeps, a launch
+    // for each (one for all, as in phase A, took as long): off_sweep counts
+    // within the group, off_elem over all.
     std::vector<int> ks;
     for (int k = 0; k < (int)S->slots.size(); ++k)
         if (S->slots[k].used) ks.push_back(k);
