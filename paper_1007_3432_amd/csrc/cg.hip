@@ -10,16 +10,16 @@
 //      issued before that sum, so the sum costs about nothing;
 //   F  one block adds the r.r deposits and sets rho, beta, the iteration
 //      count and the convergence decision.
-// In FP32, up to 512 r.r deposits (V <= 2^20), F is taken into the next A: its
-// wavefronts add the deposits, each for itself, and block 0 writes the state.
-// Two kernels an iteration then: d = 1 256 x 128 9.8 -> 8.2 us, 1024 x 256 10.6
-// -> 9.0, d = 3 8^3 x 80 10.3 -> 9.1, 16^3 x 128 14.2 -> 12.8, 20^3 x 96 18.0 ->
-// 16.3.  (By a block sum, whose barriers hold up all of A's loads, it was no
-// faster than F; from 513 deposits on the sum would outgrow the launch it
-// saves.  Adding p.q by wavefronts in B as well: 1% slower, 4% with many
-// solves.)  The state sits in two slots: A reads slot 0, B reads slot 0 and
-// block 0 writes the updated state to slot 1, F (or the next A) reads slot 1
-// and writes slot 0, so no block reads
+// In FP32, up to 512 r.r deposits (V <= 2^20), F is taken into the next A, whose
+// blocks add the deposits themselves (SumsBy) and whose block 0 writes the
+// state.  Two kernels an iteration then: d = 1 256 x 128 9.8 -> 8.2 us,
+// 1024 x 256 10.6 -> 9.0, d = 3 8^3 x 80 10.3 -> 9.1, 16^3 x 128 14.2 -> 12.7,
+// 20^3 x 96 18.0 -> 15.9.  (With the state copied as a struct, which the
+// compiler kept in LDS: 10.9 -> 22.9 on 1024 x 256.  From 513 deposits on the
+// sum would outgrow the launch it saves.  Adding p.q by wavefronts in B as
+// well: 1% slower, 4% with many solves.)  The state sits in two slots: A reads
+// slot 0, B reads slot 0 and block 0 writes the updated state to slot 1, F (or
+// the next A) reads slot 1 and writes slot 0, so no block reads
 // what its own launch writes.  Every kernel returns at once when the solve
 // has finished (still handing the state on), so the host enqueues whole
 // chunks of iterations and looks at the state only between chunks (one
@@ -217,8 +217,8 @@ thread_local HostCtx g_ctx;
 
 template <class Vec, class Lnk>
 struct Solver {
-    template <int PER = 0>
-    using PhaseA = OpPhaseA<Vec, Vec, Vec, Lnk, PER>;
+    template <int BY = kByNone>
+    using PhaseA = OpPhaseA<Vec, Vec, Vec, Lnk, BY>;
     const Geom& g;
     const hub_cg_opts& o;
     hipStream_t st;
@@ -250,10 +250,10 @@ struct Solver {
     // Phase A of an iteration after the first of its chunk: as opA, but the
     // n_rr deposits of the last phase B are not added yet.  FP32 only: FP64
     // iterations come here where the resident solver cannot run.
-    template <int PER>
+    template <int BY>
     hub_status next_sweep(const PhaseA<>& a, int n_rr) {
         if constexpr (sizeof(Vec) == 4) {
-            const PhaseA<PER> op{a.sc, a.r, a.pbuf0, a.pbuf1, a.q, a.x, a.lk, sc + 1, dep_rr, n_rr};
+            const PhaseA<BY> op{a.sc, a.r, a.pbuf0, a.pbuf1, a.q, a.x, a.lk, sc + 1, dep_rr, n_rr};
             return launch_q(g, P, op, (Vec*)yscratch, partials, st, false);
         }
         return HUB_OK;
@@ -278,17 +278,17 @@ struct Solver {
             // A reads slot 0; B reads slot 0 and writes slot 1; the next A (or
             // F) finishes B from slot 1 into slot 0.
             const int ne = elem_tiles(g.V);
-            const int next = sizeof(Vec) == 4 ? wave_deposits(ne) : 0;
+            const int next = sizeof(Vec) == 4 ? sums_by(ne, false) : kByNone;
             for (int k = 0; k < iters; ++k) {
-                if (k == 0 || next == 0)
+                if (k == 0 || next == kByNone)
                     HUB_TRY(launch_q(g, P, opA, (Vec*)yscratch, partials, st, false));
-                else if (next == 1)
-                    HUB_TRY(next_sweep<1>(opA, ne));
+                else if (next == kByWave)
+                    HUB_TRY(next_sweep<kByWave>(opA, ne));
                 else
-                    HUB_TRY(next_sweep<2>(opA, ne));
+                    HUB_TRY(next_sweep<kByBlock>(opA, ne));
                 k_phaseB_fused<Vec><<<ne, 256, 0, st>>>(sc, sc + 1, partials, P.ntiles, r, q,
                                                         g.V, dep_rr);
-                if (next == 0 || k == iters - 1)
+                if (next == kByNone || k == iters - 1)
                     k_phaseB_finish_to<<<1, 256, 0, st>>>(sc + 1, sc, dep_rr, ne);
             }
             HUB_TRY(fold_and_residual(mixed ? kModeReliable : kModeCheck));

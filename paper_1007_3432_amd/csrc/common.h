@@ -248,33 +248,57 @@ __device__ __forceinline__ void finish_phaseB(CGScalars* sc, double total) {
         sc->done = kDoneMaxIter;
 }
 
-// The sum of n <= 256 PER single-value deposits in the order of
+// The sum of n <= 256 single-value deposits in the order of
 // reduce_deposits<256, 1>, so with its bits, by every wavefront for itself:
 // all loads at once and no barrier, so that nothing else the kernel has to
 // load waits for it.
-template <int PER>
 __device__ __forceinline__ double reduce_deposits_wave(const double* __restrict__ partials,
                                                        int n) {
     constexpr int kG = 4;  // wavefronts of the 256-lane block whose order this is
     const int lane = threadIdx.x & 63;
-    double v[kG * PER];
+    double v[kG];
 #pragma unroll
-    for (int k = 0; k < kG * PER; ++k) v[k] = partials[min(64 * k + lane, n - 1)];
+    for (int k = 0; k < kG; ++k) v[k] = partials[min(64 * k + lane, n - 1)];
     double tot = 0.0;
 #pragma unroll
-    for (int k = 0; k < kG; ++k) {
-        double s = 0.0;
-#pragma unroll
-        for (int j = k; j < kG * PER; j += kG) s += 64 * j + lane < n ? v[j] : 0.0;
-        tot += wave_sum(s);
-    }
+    for (int k = 0; k < kG; ++k) tot += wave_sum(64 * k + lane < n ? v[k] : 0.0);
     return tot;
 }
 
-// PER for n deposits; 0: too many, a block or a kernel of its own adds them.
-// Measured as the last deposits of FP32 CG iterations, taken into the sweep
-// after them: 240 of them 14.2 -> 12.8 us an iteration, 375 18.0 -> 16.3.
-inline int wave_deposits(int n) { return n <= 256 ? 1 : n <= 512 ? 2 : 0; }
+// The same for n <= 512, shared among the wavefronts of the block: a quarter
+// of the sums each in 256 lanes, for one barrier.  Once in a kernel.
+__device__ __forceinline__ double reduce_deposits_block(const double* __restrict__ partials,
+                                                        int n) {
+    constexpr int kG = 4;
+    __shared__ double red[kG];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = (int)(blockDim.x >> 6);
+    for (int k = wid; k < kG; k += nw) {
+        const int b = 64 * k + lane;
+        const double v0 = partials[min(b, n - 1)], v1 = partials[min(b + 64 * kG, n - 1)];
+        double s = b < n ? v0 : 0.0;
+        s += b + 64 * kG < n ? v1 : 0.0;
+        s = wave_sum(s);
+        if (lane == 0) red[k] = s;
+    }
+    __syncthreads();
+    double tot = 0.0;
+#pragma unroll
+    for (int k = 0; k < kG; ++k) tot += red[k];
+    return tot;
+}
+
+// Who adds the deposits that a sweep takes over from the kernel before it:
+// each wavefront (kByWave, at most 256), the block (kByBlock, at most 512), or
+// a launch of its own before it (kByNone).  The wavefronts where one solve has
+// the chip to itself, us an iteration by wave and by block: d = 1 32 x 64 7.8
+// and 8.4, 256 x 128 8.3 and 8.4.  The block with more deposits (20^3 x 96, 375
+// of them: 16.4 and 16.1) and where blocks of many solves share the CUs, whose
+// wavefronts would issue four times the sums (eight served solves 258 and 246
+// ms).
+enum SumsBy { kByNone = 0, kByWave, kByBlock };
+inline int sums_by(int n, bool shared) {
+    return n > 512 ? kByNone : n > 256 || shared ? kByBlock : kByWave;
+}
 
 // The solver state as words, one a lane: a block that hands the state on loads
 // its lane's word beside its other loads, puts the new values in and stores it,
@@ -292,7 +316,7 @@ __device__ __forceinline__ void put_word(uint64_t& w, size_t offset, int lo, int
     if (threadIdx.x == offset / 8) w = (uint64_t)(uint32_t)hi << 32 | (uint32_t)lo;
 }
 
-// finish_phaseB by every wavefront for itself: the state left in *from and its
+// finish_phaseB by every block for itself: the state left in *from and its
 // n r.r deposits give what a sweep has to know of the next state, and the lead
 // block writes that state to *to.
 // A solve that has ended stays as it is.
@@ -300,7 +324,7 @@ struct NextState {
     double beta;
     int iter, done;
 };
-template <int PER>
+template <int BY>
 __device__ __forceinline__ NextState phaseB_take(const CGScalars* __restrict__ from,
                                                  CGScalars* __restrict__ to,
                                                  const double* __restrict__ dep_rr, int n,
@@ -311,7 +335,9 @@ __device__ __forceinline__ NextState phaseB_take(const CGScalars* __restrict__ f
     const double rho = from->rho, tol = from->tol2phi2, drop = from->delta2 * from->rho_ru;
     const int max_iter = from->max_iter, updates = from->reliable_updates;
     NextState s{from->beta, from->iter, from->done};
-    const double rr = reduce_deposits_wave<PER>(dep_rr, n);
+    double rr;
+    if constexpr (BY == kByWave) rr = reduce_deposits_wave(dep_rr, n);
+    else rr = reduce_deposits_block(dep_rr, n);
     if (s.done == kRunning) {
         if (!isfinite(rr)) {
             s.done = kDoneBreakdown;

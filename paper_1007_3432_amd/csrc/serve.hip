@@ -147,13 +147,13 @@ __device__ Link16 slot_link<Link16>(const SlotDesc& S) {
     return l;
 }
 
-template <class Lnk, int PER = 0>
-using SlotOp = OpPhaseA<float, float, float, Lnk, PER>;
+template <class Lnk, int BY = kByNone>
+using SlotOp = OpPhaseA<float, float, float, Lnk, BY>;
 
-// PER > 0 (batched engine): the sweep finishes the phase B before it.
-template <class Lnk, int PER = 0>
-__device__ SlotOp<Lnk, PER> slot_op(const SlotDesc& S) {
-    SlotOp<Lnk, PER> op{};
+// BY (batched engine): the sweep finishes the phase B before it.
+template <class Lnk, int BY = kByNone>
+__device__ SlotOp<Lnk, BY> slot_op(const SlotDesc& S) {
+    SlotOp<Lnk, BY> op{};
     op.sc = S.sc;
     op.r = S.r;
     op.pbuf0 = S.p0;
@@ -161,7 +161,7 @@ __device__ SlotOp<Lnk, PER> slot_op(const SlotDesc& S) {
     op.q = S.q;
     op.x = S.xlo;
     op.lk = slot_link<Lnk>(S);
-    if constexpr (PER > 0) {
+    if constexpr (BY != kByNone) {
         op.sc_b = S.sc2;
         op.dep_rr = S.dep_rr;
         op.n_rr = S.elem_tiles;
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(256) void k_serve_epoch(const SlotDesc* __restrict_
 // together had given some XCDs only long ones.  (Two slices in flight in the
 // d = 3 tile: 3% slower.)  The finalize of phase B is taken into the next sweep
 // where no solve has more than 512 deposits (cg.hip), leaving two launches an
-// iteration: 275 -> 258 ms.
+// iteration: 275 -> 246 ms.
 
 // Solve owning work item w, for offs[0 .. n) ascending from 0: a load and a
 // ballot for each 64 solves, where a binary search over the descriptors is a
@@ -379,12 +379,12 @@ __device__ inline int slot_of(const int* __restrict__ offs, int n, int w) {
 
 // Phase-A sweep of the solves slots[0 .. n) whose tiles are any but the one
 // of nx = 32.
-template <class Lnk, int PER>
+template <class Lnk, int BY>
 __global__ __launch_bounds__(256) void k_serve_A(const SlotDesc* __restrict__ slots,
                                                  const int* __restrict__ offs, int n) {
     const int j = slot_of(offs, n, blockIdx.x);
     const SlotDesc& S = slots[j];
-    auto op = slot_op<Lnk, PER>(S);
+    auto op = slot_op<Lnk, BY>(S);
     if (!op.take((int)blockIdx.x == offs[j])) return;
     const int tile = xcd_remap(blockIdx.x - offs[j], S.sweep_tiles);
     Sums2 r;
@@ -401,12 +401,12 @@ __global__ __launch_bounds__(256) void k_serve_A(const SlotDesc* __restrict__ sl
 }
 
 // The same for nx = 32, whose tile needs more registers.
-template <class Lnk, int PER>
+template <class Lnk, int BY>
 __global__ __launch_bounds__(256) void k_serve_A32(const SlotDesc* __restrict__ slots,
                                                    const int* __restrict__ offs, int n) {
     const int j = slot_of(offs, n, blockIdx.x);
     const SlotDesc& S = slots[j];
-    auto op = slot_op<Lnk, PER>(S);
+    auto op = slot_op<Lnk, BY>(S);
     if (!op.take((int)blockIdx.x == offs[j])) return;
     const int tile = xcd_remap(blockIdx.x - offs[j], S.sweep_tiles);
     store_deposit<1>(serve_tile_A_body<kSweepD3, 32, 8, 4>(&S, tile, op), S.partials, tile);
@@ -414,15 +414,12 @@ __global__ __launch_bounds__(256) void k_serve_A32(const SlotDesc* __restrict__ 
 
 using SweepKernel = void (*)(const SlotDesc*, const int*, int);
 template <class Lnk>
-static SweepKernel serve_A_kernel(bool nx32, int per) {
-    if (nx32)
-        return per == 1   ? k_serve_A32<Lnk, 1>
-               : per == 2 ? k_serve_A32<Lnk, 2>
-                          : k_serve_A32<Lnk, 0>;
-    return per == 1 ? k_serve_A<Lnk, 1> : per == 2 ? k_serve_A<Lnk, 2> : k_serve_A<Lnk, 0>;
+static SweepKernel serve_A_kernel(bool nx32, int by) {
+    if (nx32) return by == kByNone ? k_serve_A32<Lnk, kByNone> : k_serve_A32<Lnk, kByBlock>;
+    return by == kByNone ? k_serve_A<Lnk, kByNone> : k_serve_A<Lnk, kByBlock>;
 }
-static SweepKernel serve_A_kernel(bool nx32, bool f16, int per) {
-    return f16 ? serve_A_kernel<Link16>(nx32, per) : serve_A_kernel<Link32>(nx32, per);
+static SweepKernel serve_A_kernel(bool nx32, bool f16, int by) {
+    return f16 ? serve_A_kernel<Link16>(nx32, by) : serve_A_kernel<Link32>(nx32, by);
 }
 
 // Phase B with the sweep's reduction taken in (k_phaseB_fused).
@@ -879,16 +876,16 @@ hub_status run_epoch(hub_server* S) {
         HUB_HIP(hipMemcpyAsync(S->offs_d, S->offs_h, sizeof(int) * 3 * m, hipMemcpyHostToDevice,
                                st));
         const int *oA = S->offs_d, *oR = S->offs_d + m, *oE = S->offs_d + 2 * m;
-        const int next = wave_deposits(most_rr);
+        const int next = sums_by(most_rr, true);
         for (int it = 0; it < iters; ++it) {
             for (int k = 0; k < 2; ++k) {
                 const auto& A = pa[k];
                 if (A.count == 0) continue;
-                serve_A_kernel(k == 1, f16, it == 0 ? 0 : next)<<<A.tiles, 256, A.lds, st>>>(
+                serve_A_kernel(k == 1, f16, it == 0 ? kByNone : next)<<<A.tiles, 256, A.lds, st>>>(
                     descp + A.first, oA + A.first, A.count);
             }
             k_serve_B<<<tot_elem, 256, 0, st>>>(descp, oE, n);
-            if (next == 0 || it == iters - 1) k_serve_finB<<<n, 256, 0, st>>>(descp);
+            if (next == kByNone || it == iters - 1) k_serve_finB<<<n, 256, 0, st>>>(descp);
         }
         k_serve_fold<<<tot_elem, 256, 0, st>>>(descp, oE, n);
         for (const Group& gr : groups)

@@ -170,7 +170,7 @@ struct OpApply {
 // p is double-buffered by iteration parity so halo reads never see a p_new.
 // The p.q deposits are added either by a one-block finalize (finish(), which
 // sets alpha) or by the next kernel's blocks themselves.
-template <class Acc, class Vec, class XVec, class Lnk, int PER = 0>
+template <class Acc, class Vec, class XVec, class Lnk, int BY = kByNone>
 struct OpPhaseA {
     using acc_t = Acc;
     struct center_t {
@@ -194,8 +194,8 @@ struct OpPhaseA {
     Vec* q;
     XVec* x;
     Lnk lk;
-    // PER > 0: where the last phase B left its state and its r.r deposits (at
-    // most 256 PER), which this sweep has to finish.  Otherwise *sc is the state.
+    // BY (SumsBy): where the last phase B left its state and its r.r deposits,
+    // which this sweep has to finish.  Without, *sc is the state.
     const CGScalars* sc_b;
     const double* dep_rr;
     int n_rr;
@@ -204,12 +204,12 @@ struct OpPhaseA {
     Vec* pnew;
     Acc beta, alpha, gamma;
     // The state this sweep starts from; false when the solve is not running.
-    // With PER every block adds phase B's deposits itself and the lead block
+    // With BY every block adds phase B's deposits itself and the lead block
     // writes the state to *sc, where the next phase B reads it.  All lanes.
     __device__ bool take(bool lead) {
         NextState s;
-        if constexpr (PER > 0) {
-            s = phaseB_take<PER>(sc_b, sc, dep_rr, n_rr, lead);
+        if constexpr (BY != kByNone) {
+            s = phaseB_take<BY>(sc_b, sc, dep_rr, n_rr, lead);
             alpha = (Acc)sc_b->alpha;
             gamma = (Acc)sc_b->gamma;
         } else {
