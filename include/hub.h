@@ -121,7 +121,7 @@ HUB_API hub_status hub_apply_MtM(const hub_lattice* lat, const void* links,
 
 /* Solve (M^T M) x = phi by conjugate gradient from x = 0 (Sec. 4.1).
  * sigma, phi: device FP64[nx^d * nt]; x: device FP64[nx^d * nt], output.
- * opts->bulk = HUB_F64: Hestenes-Stiefel CG in FP64 throughout.
+ * opts->bulk = HUB_F64: CG in FP64 throughout.
  * opts->bulk = HUB_F32: mixed precision with reliable updates: vectors r, p,
  *   q and the correction x_lo in FP32, links per opts->link, dot products
  *   accumulated in FP64; every opts->reliable_every iterations (and whenever
@@ -129,10 +129,13 @@ HUB_API hub_status hub_apply_MtM(const hub_lattice* lat, const void* links,
  *   solution and r is replaced by the FP64 true residual phi - Q x.
  * Convergence is always decided on the FP64 true residual.  With bulk =
  * HUB_F64 a lattice of at most 2048 sites is solved in one workgroup (one
- * kernel launch), and one that fits the registers of the chip (up to about a
- * million sites: nx^(d-1) at most 512) by one block per CU, a launch per 1000
- * iterations; such launches of several threads follow each other.  (In the
- * latter the sums are arranged after Chronopoulos and Gear.)  Otherwise each
+ * kernel launch), and one that fits the registers of the chip by one block per
+ * CU, a launch per 1000 iterations; such launches of several threads follow
+ * each other.  There beta is taken from a square expanded before the new
+ * residual exists (one grid sum an iteration), and a true residual that
+ * replaces the iterated one starts the directions anew; otherwise the
+ * arrangement is Hestenes and Stiefel's, and the direction is kept.
+ * Otherwise, and where the resident solve breaks down, each
  * iteration is a few kernels replayed in chunks from HIP graphs.  The device
  * workspace (about six V-vectors) and the chunk graphs are kept per
  * host thread after the call: the next solve on that thread reuses the

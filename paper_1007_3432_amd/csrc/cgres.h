@@ -3,27 +3,34 @@
 // for one workgroup and small enough that the vectors and links fit the
 // registers of one block per CU (restile.h).
 //
-// Plain CG: the sums and the directions are arranged after Chronopoulos and
-// Gear (1989), so that an iteration has one grid sum, over x, r, p, s = Q p:
-//   1. w = Q r; its rim goes to the neighbours and the block's r.r and r.w to
-//      the grid sum (gridsum.h);
-//   2. beta = r.r / (r.r before), p.Qp = r.w - beta r.r / (alpha before),
-//      alpha = r.r / p.Qp; p = r + beta p, s = w + beta s, x += alpha p,
-//      r -= alpha s.
-//      On the halo, where w has come from the neighbours, s and r follow the
+// Plain CG with one grid sum an iteration, over x, r and p:
+//   1. q = Q p; its rim goes to the neighbours and the block's r.r, p.q, r.q
+//      and q.q to the grid sum (gridsum.h);
+//   2. alpha = r.r / p.q; |r - alpha q|^2 = r.r - 2 alpha r.q + alpha^2 q.q over r.r
+//      gives beta before the new r exists (after Saad 1985 and Meurant 1987); x +=
+//      alpha p, r -= alpha q, p = r + beta p.
+//      On the halo, where q has come from the neighbours, r and p follow the
 //      same recurrences: the block keeps the values that their owners have.
+// Only beta rests on the expanded square: alpha and the convergence test take
+// the r.r that is summed anew, and Q p is formed anew, in every iteration.  So
+// the iterations are those of Hestenes and Stiefel's arrangement also where the
+// coupling is strong.  (With Q p and p.Qp by recurrence, after Chronopoulos and
+// Gear, which is as fast, d = 1 64 x 128 at U = -6 took up to 22% more iterations
+// to 1e-12, and after a residual had been replaced the p.Qp of one of the next
+// steps came out negative: in 22 of 110 solves between U = -2 and -7 emulated on
+// the host, all of which converge now.)
 // The kernel ends when r.r meets tol, after a number of iterations, or when
 // it cannot go on; the state is in memory then.  Convergence is decided
 // between launches as in the other solvers: the true residual phi - Q x
-// replaces r, and if it does not meet tol the iteration goes on from it,
-// keeping p; the next p.Qp is then r.w + 2 beta r.s + beta^2 (p.Qp before), as
-// r has lost its exact orthogonality to the step before.
+// replaces r, and if it does not meet tol the iteration starts again from it, p
+// = r.  (Keeping p, as the multi-kernel solver does, took as many iterations in
+// most of those solves, and one then went on replacing without an end.)
 //
 // What bounds an iteration is the grid sum (1.8 to 2.5 us), the halo read after
 // it and the LDS traffic of the stencils, where it was three kernels and 80
 // bytes a site of memory traffic.  Before and now, us an iteration: d = 1
-// 256 x 128 9.4 and 2.9, 4096 x 128 15.2 and 4.2, 2048 x 512 20.5 and 4.9; d = 2
-// 33 x 60 11.9 and 3.3; d = 3 8^3 x 80 12.1 and 3.2, 16^3 x 128 17.2 and 5.7.
+// 256 x 128 9.4 and 3.0, 4096 x 128 15.2 and 4.2, 2048 x 512 20.5 and 4.8; d = 2
+// 33 x 60 11.9 and 3.4; d = 3 8^3 x 80 12.1 and 3.3, 16^3 x 128 17.2 and 5.8.
 // (Hestenes and Stiefel's arrangement, with two grid sums an iteration, took
 // 4.5, 5.7, 7.0, 5.3, 4.8 and 11.0.)
 #pragma once
@@ -39,90 +46,70 @@ __global__ __launch_bounds__(kResBlock) void k_cg_resident(ResArgs a) {
     extern __shared__ __align__(16) double res_lds[];
     ResTile<D, WHOLE, KO, KY, KH> T;
     T.init(a, res_lds);
-    GridSum gs{a.slots, res_lds, a.limit, 0};
+    GridSum<4> gs{a.slots, res_lds, a.limit, 0};
     auto give_up = [&]() {
         if (threadIdx.x == 0)
             __hip_atomic_store(&a.st->given_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    double x[KO], r[KO], p[KO], s[KO];
-    double rh[KH], sh[KH];
+    double x[KO], r[KO], p[KO];
+    double rh[KH], ph[KH];
     ResState c{};
-    if (a.mode == kResFirst) {
+    if (a.mode != kResFirst) c = *a.st;
+    const double* r0 = a.mode == kResFirst ? a.phi : a.R;
+    const double* p0 = a.mode == kResOn ? a.P : r0;
 #pragma unroll
-        for (int k = 0; k < KO; ++k) {
-            r[k] = T.ook[k] ? *at(a.phi, T.ogi[k]) : 0.0;
-            x[k] = p[k] = s[k] = 0.0;
-        }
+    for (int k = 0; k < KO; ++k) {
+        r[k] = T.ook[k] ? *at(r0, T.ogi[k]) : 0.0;
+        p[k] = T.ook[k] ? *at(p0, T.ogi[k]) : 0.0;
+        x[k] = T.ook[k] && a.mode != kResFirst ? *at(a.x, T.ogi[k]) : 0.0;
+    }
 #pragma unroll
-        for (int k = 0; k < KH; ++k) {
-            rh[k] = *at(a.phi, T.hgi[k]);
-            sh[k] = 0.0;
-        }
-    } else {
-        c = *a.st;
-#pragma unroll
-        for (int k = 0; k < KO; ++k) {
-            r[k] = T.ook[k] ? *at(a.R, T.ogi[k]) : 0.0;
-            p[k] = T.ook[k] ? *at(a.P, T.ogi[k]) : 0.0;
-            s[k] = T.ook[k] ? *at(a.S, T.ogi[k]) : 0.0;
-            x[k] = T.ook[k] ? *at(a.x, T.ogi[k]) : 0.0;
-        }
-#pragma unroll
-        for (int k = 0; k < KH; ++k) {
-            rh[k] = *at(a.R, T.hgi[k]);
-            sh[k] = *at(a.S, T.hgi[k]);
-        }
+    for (int k = 0; k < KH; ++k) {
+        rh[k] = *at(r0, T.hgi[k]);
+        ph[k] = *at(p0, T.hgi[k]);
     }
 
-    int mode = a.mode, n = 0;
-    for (;;) {
-        double w[KO];
-        T.apply_q(r, rh, w);
-        T.publish(w);
-        double part0 = 0.0, part1 = 0.0;
+    for (int n = 0;; ++n) {
+        double q[KO];
+        T.apply_q(p, ph, q);
+        T.publish(q);
+        double part[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < KO; ++k) {
-            part0 += r[k] * r[k];
-            part1 += r[k] * w[k];
+            part[0] += r[k] * r[k];
+            part[1] += p[k] * q[k];
+            part[2] += r[k] * q[k];
+            part[3] += q[k] * q[k];
         }
-        gs.deposit(part0, part1);
-        double rr, rw;
-        if (!gs.wait(rr, rw)) return give_up();
-        double wh[KH];
-        T.fetch(wh);
-        if (mode == kResFirst) c.phi2 = rr;
+        gs.deposit(part);
+        double sum[4];
+        if (!gs.wait(sum)) return give_up();
+        double qh[KH];
+        T.fetch(qh);
+        const double rr = sum[0], pq = sum[1];
+        const bool first = n == 0 && a.mode != kResOn;
+        if (first && a.mode == kResFirst) c.phi2 = rr;
         // (A residual just replaced has not met tol by the sum that decides.)
         if (!isfinite(rr)) c.done = kDoneBreakdown;
-        else if (rr <= a.tol2 * c.phi2 && mode != kResReplaced) c.done = kDoneIterConverged;
+        else if (rr <= a.tol2 * c.phi2 && !(first && a.mode == kResReplaced))
+            c.done = kDoneIterConverged;
         else if (c.iter >= a.max_iter) c.done = kDoneMaxIter;
+        else if (n < a.iters && (!(pq > 0.0) || !isfinite(pq))) c.done = kDoneBreakdown;
         if (c.done != kRunning || n == a.iters) break;
-        const double beta = mode == kResFirst ? 0.0 : rr / c.rho;
-        double pq = rw;
-        if (mode == kResOn) pq = rw - beta * rr / c.alpha;
-        else if (mode == kResReplaced) pq = rw + 2.0 * beta * c.rs + beta * beta * c.pq;
-        if (!(pq > 0.0) || !isfinite(pq)) {
-            c.done = kDoneBreakdown;
-            break;
-        }
-        const double alpha = rr / pq;
-        c.pq = pq;
-        c.alpha = alpha;
-        c.rho = rr;
-        mode = kResOn;
+        const double inv = 1.0 / pq, alpha = rr * inv;
+        const double beta = fmax(1.0 + (alpha * sum[3] - 2.0 * sum[2]) * inv, 0.0);
 #pragma unroll
         for (int k = 0; k < KO; ++k) {
-            p[k] = r[k] + beta * p[k];
-            s[k] = w[k] + beta * s[k];
             x[k] = x[k] + alpha * p[k];
-            r[k] = r[k] - alpha * s[k];
+            r[k] = r[k] - alpha * q[k];
+            p[k] = r[k] + beta * p[k];
         }
 #pragma unroll
         for (int k = 0; k < KH; ++k) {
-            sh[k] = wh[k] + beta * sh[k];
-            rh[k] = rh[k] - alpha * sh[k];
+            rh[k] = rh[k] - alpha * qh[k];
+            ph[k] = rh[k] + beta * ph[k];
         }
         ++c.iter;
-        ++n;
     }
 #pragma unroll
     for (int k = 0; k < KO; ++k)
@@ -131,13 +118,9 @@ __global__ __launch_bounds__(kResBlock) void k_cg_resident(ResArgs a) {
             *at_w(a.x, i) = x[k];
             *at_w(a.R, i) = r[k];
             *at_w(a.P, i) = p[k];
-            *at_w(a.S, i) = s[k];
         }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         // Not given_up, which another block may write.
-        a.st->rho = c.rho;
-        a.st->alpha = c.alpha;
-        a.st->pq = c.pq;
         a.st->phi2 = c.phi2;
         a.st->iter = c.iter;
         a.st->done = c.done;
@@ -159,7 +142,7 @@ __global__ __launch_bounds__(kResBlock) void k_pcg_resident(ResArgs a) {
     extern __shared__ __align__(16) double res_lds[];
     ResTile<D, WHOLE, KO, KY, KH> T;
     T.init(a, res_lds);
-    GridSum gs{a.slots, res_lds, a.limit, 0};
+    GridSum<1> gs{a.slots, res_lds, a.limit, 0};
     auto give_up = [&]() {
         if (threadIdx.x == 0)
             __hip_atomic_store(&a.st->given_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -184,19 +167,19 @@ __global__ __launch_bounds__(kResBlock) void k_pcg_resident(ResArgs a) {
     int mode = a.mode, n = 0;
     for (;;) {
         double v[KO], t[KO], vh[KH];
-        double part = 0.0;
+        double part[1] = {0.0}, sum[1];
 #pragma unroll
         for (int k = 0; k < KO; ++k) {
             v[k] = r[k];
-            part += r[k] * r[k];
+            part[0] += r[k] * r[k];
         }
         T.publish(v);
-        gs.deposit(part, 0.0);
+        gs.deposit(part);
         if (!T.exchange()) return give_up();
         T.fetch(vh);
         T.apply_q(v, vh, t);
-        double rr, none;
-        if (!gs.wait(rr, none)) return give_up();
+        if (!gs.wait(sum)) return give_up();
+        const double rr = sum[0];
         if (mode == kResFirst) c.phi2 = rr;
         // (A residual just replaced has not met tol by the sum that decides.)
         if (!isfinite(rr)) c.done = kDoneBreakdown;
@@ -218,12 +201,12 @@ __global__ __launch_bounds__(kResBlock) void k_pcg_resident(ResArgs a) {
             T.fetch(vh);
             T.apply_q(v, vh, t);
         }
-        part = 0.0;
+        part[0] = 0.0;
 #pragma unroll
-        for (int k = 0; k < KO; ++k) part += r[k] * v[k];
-        double rz;
-        gs.deposit(part, 0.0);
-        if (!gs.wait(rz, none)) return give_up();
+        for (int k = 0; k < KO; ++k) part[0] += r[k] * v[k];
+        gs.deposit(part);
+        if (!gs.wait(sum)) return give_up();
+        const double rz = sum[0];
         if (!(rz > 0.0) || !isfinite(rz)) {
             c.done = kDoneBreakdown;
             break;
@@ -231,7 +214,7 @@ __global__ __launch_bounds__(kResBlock) void k_pcg_resident(ResArgs a) {
         const double beta = mode == kResOn ? rz / c.rho : 0.0;
         c.rho = rz;
         mode = kResOn;
-        part = 0.0;
+        part[0] = 0.0;
 #pragma unroll
         for (int k = 0; k < KO; ++k) p[k] = v[k] + beta * p[k];
         T.publish(p);
@@ -239,10 +222,10 @@ __global__ __launch_bounds__(kResBlock) void k_pcg_resident(ResArgs a) {
         T.fetch(vh);
         T.apply_q(p, vh, t);
 #pragma unroll
-        for (int k = 0; k < KO; ++k) part += p[k] * t[k];
-        double pq;
-        gs.deposit(part, 0.0);
-        if (!gs.wait(pq, none)) return give_up();
+        for (int k = 0; k < KO; ++k) part[0] += p[k] * t[k];
+        gs.deposit(part);
+        if (!gs.wait(sum)) return give_up();
+        const double pq = sum[0];
         if (!(pq > 0.0) || !isfinite(pq)) {
             c.done = kDoneBreakdown;
             break;

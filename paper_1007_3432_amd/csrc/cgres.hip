@@ -43,7 +43,7 @@ ResPlan plan_resident(const Geom& g, int max_blocks) {
             const int own = ceil_div(Tz * Tt, G), rim = ceil_div(2 * H * Tt + Tz, G),
                       halo = ceil_div(2 * (Tz + 2 * H) + 4 * H * Tt, G);
             const size_t lds =
-                8 * (GridSum::kLdsDoubles + 2 + (size_t)inner * ((size_t)(Tz + 4 * H) * (Tt + 2) +
+                8 * (GridSum<kGridSumMax>::kLdsDoubles + 2 + (size_t)inner * ((size_t)(Tz + 4 * H) * (Tt + 2) +
                                            (size_t)(Tz + 2 * H) * (Tt + 1)));
             if (lds > kResLdsMax) continue;
             for (int l = 0; l < kResLevelCount; ++l) {
@@ -88,30 +88,25 @@ __global__ __launch_bounds__(256) void k_res_reset(uint64_t* slots, uint64_t* fl
     }
 }
 
-// r = phi - z, and the deposits of |r|^2 and r.s.
+// r = phi - z, and the deposits of |r|^2.
 __global__ __launch_bounds__(256) void k_res_recompute(const double* __restrict__ phi,
                                                        const double* __restrict__ z,
-                                                       const double* __restrict__ s,
                                                        double* __restrict__ r, int V,
                                                        double* partials) {
-    double part[2] = {0.0, 0.0};
+    double part[1] = {0.0};
     for (int i = blockIdx.x * 256 + threadIdx.x; i < V; i += gridDim.x * 256) {
         const double d = phi[i] - z[i];
         r[i] = d;
         part[0] += d * d;
-        part[1] += d * s[i];
     }
-    deposit<256, 2>(part, partials, blockIdx.x);
+    deposit<256, 1>(part, partials, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_res_recompute_finish(const double* partials, int n,
                                                               ResState* st) {
-    double tot[2];
-    reduce_deposits<256, 2>(partials, n, tot);
-    if (threadIdx.x == 0) {
-        st->rho_true = tot[0];
-        st->rs = tot[1];
-    }
+    double tot[1];
+    reduce_deposits<256, 1>(partials, n, tot);
+    if (threadIdx.x == 0) st->rho_true = tot[0];
 }
 
 // Products with Q of one launch: about 5 ms, after which other streams and threads
@@ -162,7 +157,7 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
     const size_t vb = al(8 * (size_t)g.V);
     const size_t sb = al(8 * (kSlotWords + kFlagWords)), fb = al(24 * (size_t)nf);
     char* ws = nullptr;
-    hub_status r = solver_workspace(6 * vb + sb + 256 + fb, &ws);
+    hub_status r = solver_workspace(5 * vb + sb + 256 + fb, &ws);
     if (r != HUB_OK) return r;
     SolverHost host;
     r = solver_host(&host);
@@ -176,17 +171,14 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
     a.A = (const double*)ws;
     a.R = (double*)(ws + vb);
     a.P = (double*)(ws + 2 * vb);
-    a.S = (double*)(ws + 3 * vb);
-    a.W = (double*)(ws + 4 * vb);  // two vectors
-    a.slots = (uint64_t*)(ws + 6 * vb);
+    a.W = (double*)(ws + 3 * vb);  // two vectors
+    a.slots = (uint64_t*)(ws + 5 * vb);
     a.flags = a.slots + kSlotWords;
-    a.st = (ResState*)(ws + 6 * vb + sb);
-    a.f = (double*)(ws + 6 * vb + sb + 256);
+    a.st = (ResState*)(ws + 5 * vb + sb);
+    a.f = (double*)(ws + 5 * vb + sb + 256);
     a.nf = nf;
-    if (pcg) {
-        a.S = a.P;  // no s; the recompute's r.s is not used
+    if (pcg)
         HUB_HIP(hipMemcpyAsync((void*)a.f, factors, 24 * (size_t)nf, hipMemcpyHostToDevice, st));
-    }
     a.phi = phi;
     a.x = x;
     a.tol2 = o.tol * o.tol;
@@ -210,8 +202,8 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
         if (q != HUB_OK) return q;
         const int blocks = std::min(256, ceil_div(g.V, 256));
         double* part = (double*)a.slots;  // refilled before the next launch
-        static_assert(2 * 256 <= kSlotWords, "deposits fit the slots");
-        k_res_recompute<<<blocks, 256, 0, st>>>(phi, z, a.S, a.R, g.V, part);
+        static_assert(256 <= kSlotWords, "deposits fit the slots");
+        k_res_recompute<<<blocks, 256, 0, st>>>(phi, z, a.R, g.V, part);
         k_res_recompute_finish<<<1, 256, 0, st>>>(part, blocks, a.st);
         HUB_HIP(hipGetLastError());
         return fetch();
@@ -238,7 +230,9 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
             r = fetch();
             if (r != HUB_OK) return r;
         }
-        if (s->given_up) return HUB_OK;
+        // A breakdown is left to the multi-kernel solver as well: it decides, and
+        // counts its steps, as it does for the lattices that come to it first.
+        if (s->given_up || s->done == kDoneBreakdown) return HUB_OK;
         done = s->done;
         a.mode = kResOn;
         if (done != kDoneIterConverged) continue;
@@ -251,7 +245,7 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
         if (r != HUB_OK) return r;
         ++recomputes;
         if (s->rho_true <= a.tol2 * s->phi2) done = kDoneConverged;
-        else if (!std::isfinite(s->rho_true)) done = kDoneBreakdown;
+        else if (!std::isfinite(s->rho_true)) return HUB_OK;
         else if (s->iter >= o.max_iter) done = kDoneMaxIter;
         else done = kRunning;
         a.mode = kResReplaced;
@@ -274,9 +268,8 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
     if (out) *out = stats;
     if (stats.status != HUB_OK)
         return set_error(HUB_E_NOCONV,
-                         "CG did not converge: %d iterations, true relative residual %.3e%s",
-                         s->iter, stats.true_rel_resid,
-                         done == kDoneBreakdown ? " (breakdown)" : "");
+                         "CG did not converge: %d iterations, true relative residual %.3e",
+                         s->iter, stats.true_rel_resid);
     return HUB_OK;
 }
 

@@ -30,7 +30,7 @@ namespace hub {
 
 // Positions a lane handles at most: its own sites, the sites around the tile
 // where y is formed, and the halo.  Each level is a kernel; in CG a lane
-// holds 15 words for each of the first, 4 and 6 for each of the others, and
+// holds 13 words for each of the first, 4 and 6 for each of the others, and
 // two more for each of the first two where z is whole.  `whole`: that fits too.
 struct ResLevel {
     int own, rim, halo;
@@ -43,12 +43,9 @@ constexpr int kResLevelCount = 10;
 constexpr int kResBlock = 512;
 
 struct ResState {
-    double rho;       // r.r before the step that r has taken last
-    double alpha;     // of that step
-    double pq;        // p.Qp of that step
+    double rho;       // preconditioned: r.z of the last step
     double phi2;
     double rho_true;  // |phi - Q x|^2 of the last recompute
-    double rs;        // r.s after it
     int32_t iter;
     int32_t done;     // kRunning, kDoneIterConverged, kDoneBreakdown, kDoneMaxIter
     int32_t given_up;
@@ -65,7 +62,7 @@ struct ResArgs {
     const double* A;
     const double* phi;
     double* x;
-    double *R, *P, *S;  // r, p and s between launches
+    double *R, *P;  // r and p between launches
     double* W;   // 2 V: rims between blocks
     uint64_t* flags;  // kMaxResidentBlocks, 64 bytes apart, 0 when a launch starts
     uint64_t* slots;
@@ -110,7 +107,7 @@ struct ResTile {
     static constexpr int H = WHOLE ? 0 : 1;  // z halo of y; v has twice that
     // LDS, in doubles: the sums, the give-up mark, P, Y, and one spare element
     // that positions past the end write.  Indices are LDS byte addresses.
-    static constexpr int kMark = GridSum::kLdsDoubles, kP = kMark + 1;
+    static constexpr int kMark = GridSum<kGridSumMax>::kLdsDoubles, kP = kMark + 1;
 
     double kappa;
     int I, ZP, ZY;  // inner sites; z extents of P and Y
