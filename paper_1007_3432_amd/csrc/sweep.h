@@ -148,11 +148,10 @@ inline void plan_rows(const Geom& g, SweepPlan* p) {
             const int tiles = cy * cz;
             // About two blocks per CU, chunks of 2 to 16 slices (256, 768 and
             // 1024 blocks were up to 40% slower on one lattice or another).
-            const long long tcl = ((long long)g.nt * tiles + env_int("RB",512)-1) / env_int("RB",512);
+            const long long tcl = ((long long)g.nt * tiles + 511) / 512;
             const int tc = (int)(tcl < 2 ? 2 : (tcl > 16 ? 16 : tcl));
             const int chunks = ceil_div(g.nt, tc);
             for (int l = 0; l < kRowsLevelCount; ++l) {
-                if (env_int("RL",-1) >= 0 && env_int("RL",-1) != l) continue;
                 const RowsLevel& K = kRowsLevels[l];
                 if (own > K.own * kRowsBlock || hx > K.halo_x * kRowsBlock ||
                     hy > K.halo_y * kRowsBlock)
