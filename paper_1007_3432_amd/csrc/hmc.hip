@@ -66,11 +66,12 @@ __global__ __launch_bounds__(256) void k_force(Geom g, double* __restrict__ sigm
 }
 
 // The same force for even nx, two x-adjacent sites per lane (16-byte loads
-// and stores, non-temporal for the force and for a sigma that is not written
-// back, as in k_apply_M2: d = 1 2048 x 512 7.3 -> 6.4 us, d = 3 32^3 x 256 52.5
-// -> 42.3, streamed from HBM; the x neighbours of the pair are its own two values and one
-// more site on each side).  Each site's arithmetic is that of k_force, in
-// the same order.
+// and stores, the force's with the non-temporal hint for the reason given at
+// k_apply_M: the same buffers again, d = 1 2048 x 512 5.6 -> 4.9 us, d = 3 32^3 x
+// 256 34.8 -> 34.4, buffers in turn 7.7 -> 6.7 and 53 -> 33; with the hint on
+// the loads of sigma too 6.2 and 43, 6.8 and 43; the x neighbours of the pair are
+// its own two values and one more site on each side).  Each site's arithmetic is
+// that of k_force, in the same order.
 template <int MODE, int D>
 __global__ __launch_bounds__(256) void k_force2(Geom g, double* __restrict__ sigma,
                                                 const double* __restrict__ x,
@@ -106,14 +107,7 @@ __global__ __launch_bounds__(256) void k_force2(Geom g, double* __restrict__ sig
         rest = q;
     }
     const double sg = sp == 0 ? g.lscale : -g.lscale;
-    const double2 xi = ld2v(x + i);
-    double2 sv;
-    if constexpr (MODE == kKickDrift) {
-        sv = ld2v(sigma + i);
-    } else {
-        const D2 w = ld2_nt(sigma + i);
-        sv = make_double2(w.a, w.b);
-    }
+    const double2 sv = ld2v(sigma + i), xi = ld2v(x + i);
     double sn_a, cs_a, sn_b, cs_b;
     sincos(sv.x, &sn_a, &cs_a);
     sincos(sv.y, &sn_b, &cs_b);

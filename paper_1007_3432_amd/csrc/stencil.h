@@ -1464,11 +1464,15 @@ __global__ __launch_bounds__(256) void k_gen_pass2(Geom g, Op op,
 
 // ---------------------------------------------------------------------------
 // Single M or M^T (hub_apply_M): one lane per site, neighbours through L1/L2.
-// Bound by memory: the result is stored, and (two sites a lane) the links are
-// loaded, with the non-temporal hint, so that the L2s keep the input rows that
-// neighbouring blocks read again: M^T in FP64, streamed from HBM, d = 1 2048 x
-// 512 6.7 -> 5.6 us (4.5 TB/s), d = 3 32^3 x 256 48.8 -> 40.3 (5.0), 16^3 x 160
-// 5.5 -> 5.0; d = 2 99^2 x 100 (one site a lane, store only) 8.8 -> 7.0.
+// Bound by memory: the result is stored with the non-temporal hint, so that the
+// caches keep the inputs, which neighbouring blocks (and often the next call)
+// read again.  M^T in FP64, plain stores and now, us: the same buffers again, d =
+// 1 2048 x 512 4.2 -> 3.7, d = 3 16^3 x 160 4.1 -> 3.7, 32^3 x 256 30.3 -> 30.3;
+// buffers taken in turn (700 MB of them; of 32^3 x 256 the inputs then stay in
+// the Infinity Cache) 7.2 -> 6.1, 5.8 -> 5.4, 50 -> 29.  What reads the result
+// next finds it in HBM: M and then M^T 8.4 -> 7.0, 7.5 -> 7.1, but 58 -> 75.
+// (The hint on the loads of the links as well made a call on the same buffers 5.0,
+// 4.8 and 40.8, without being faster on others: 6.1, 5.2 and 40.)
 template <class Acc, class Vec, class Lnk, bool TRANSPOSE>
 __global__ __launch_bounds__(256) void k_apply_M(Geom g, Lnk lk, const Vec* x, Vec* y) {
     const int i = xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
@@ -1534,13 +1538,13 @@ __global__ __launch_bounds__(256) void k_apply_M2(Geom g, const double* __restri
     double vb = xc.b - g.kappa * hop_b;
     if (!TRANSPOSE) {
         const int sm = s == 0 ? g.nt - 1 : s - 1;
-        const D2 a = ld2_nt(A + i), xm = ld2(x + n + sm * g.vs);
+        const D2 a = ld2(A + i), xm = ld2(x + n + sm * g.vs);
         va += a.a * xm.a;
         vb += a.b * xm.b;
     } else {
         const int sp = s == g.nt - 1 ? 0 : s + 1;
         const int ip = n + sp * g.vs;
-        const D2 a = ld2_nt(A + ip), xp = ld2(x + ip);
+        const D2 a = ld2(A + ip), xp = ld2(x + ip);
         va += a.a * xp.a;
         vb += a.b * xp.b;
     }
