@@ -131,9 +131,9 @@ bool res_enabled() {
 
 // One launch at a time on a device: its blocks wait for each other, so all
 // must find a place.
-std::mutex& resident_mutex(int device) {
-    static std::mutex m[64];
-    return m[device & 63];
+FairLock& resident_lock(int device) {
+    static FairLock lock[64];
+    return lock[device & 63];
 }
 
 hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* phi, double* x,
@@ -214,7 +214,7 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
     int done = kRunning, recomputes = 0;
     while (done == kRunning) {
         {
-            std::lock_guard<std::mutex> lk(resident_mutex(dev));
+            std::lock_guard<FairLock> lk(resident_lock(dev));
             k_res_reset<<<8, 256, 0, st>>>(a.slots, a.flags, a.st);
             void* args[] = {&a};
             const hipError_t e = hipLaunchCooperativeKernel(

@@ -1,10 +1,10 @@
 // Host-side internals of libhub shared between translation units.
 #pragma once
 
-#include <mutex>
 #include <string>
 
 #include "common.h"
+#include "fairlock.h"
 
 namespace hub {
 
@@ -80,7 +80,7 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
                              const hub_cg_opts& o, const double* factors, int nf,
                              hub_cg_stats* out, hipStream_t st, bool* ran);
 // Held while a kernel whose blocks wait for each other runs on the device.
-std::mutex& resident_mutex(int device);
+FairLock& resident_lock(int device);
 
 // HMC (hmc.hip; arguments already validated).
 hub_status hmc_force(const Geom& g, const double* sigma, const double* x, double* F,

@@ -844,7 +844,7 @@ hub_status run_epoch(hub_server* S) {
     HUB_HIP(hipMemcpyAsync(S->desc_d, S->desc_h, sizeof(SlotDesc) * n, hipMemcpyHostToDevice,
                            S->stream));
     int iters = S->opts.cg.reliable_every;
-    std::unique_lock<std::mutex> resident;
+    std::unique_lock<FairLock> resident;
     const SlotDesc* descp = S->desc_d;
     const bool f16 = S->opts.cg.link == HUB_F16;
     if (S->opts.engine == 1) {
@@ -868,7 +868,7 @@ hub_status run_epoch(hub_server* S) {
                              : (const void*)k_serve_epoch<Link32>;
         // Until the kernel has ended (below), no other one whose blocks wait
         // for each other may take CUs from it.
-        resident = std::unique_lock<std::mutex>(resident_mutex(S->device));
+        resident = std::unique_lock<FairLock>(resident_lock(S->device));
         HUB_HIP(hipLaunchCooperativeKernel(fn, dim3(S->coop_grid), dim3(256), args,
                                            kServeLdsBytes, S->stream));
     } else {

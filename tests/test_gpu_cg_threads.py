@@ -1,0 +1,67 @@
+"""FP64 hub_cg_solve from several threads: the launches of solves that stay on the
+chip follow each other, and nobody waits longer than for those before it."""
+import threading
+
+import numpy as np
+import pytest
+
+from paper_1007_3432_amd import hub, inputs
+from tests import hubtest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    hubtest.ensure_built()
+
+
+class Problem:
+    def __init__(self, shape, max_iter, tol=1e-10):
+        import torch
+        self.lat = hub.lattice(*shape)
+        sigma, phi = inputs.sigma_eta(*shape, seed=12)
+        self.sigma, self.phi = hubtest.to_dev(sigma), hubtest.to_dev(phi)
+        self.x = hubtest.empty(self.lat.volume, hub.F64)
+        self.opts = hub.cg_opts(hub.F64, tol=tol, max_iter=max_iter)
+        self.stream = torch.cuda.Stream()
+
+    def solve(self):
+        import torch
+        with torch.cuda.stream(self.stream):
+            return hub.hub_cg_solve(self.lat, self.sigma, self.phi, self.x, self.opts,
+                                    raise_on_noconv=False)
+
+
+def test_short_solve_beside_a_long_one():
+    """A thread that solves without a pause, eight or more launches a solve:
+    another thread's solves of one launch each wait for one or two of those
+    launches, not for the solve they belong to."""
+    import torch
+    hubtest.log_case("cg threads: short beside long")
+    long, short = Problem((1, 4096, 128), 200000), Problem((3, 5, 20), 300)
+    assert long.solve()["iters"] > 8000
+    alone = short.solve()
+    x = short.x.cpu().numpy()
+    torch.cuda.synchronize()
+    count, stop = [0], threading.Event()
+
+    def work():
+        while not stop.is_set():
+            long.solve()
+            count[0] += 1
+
+    t = threading.Thread(target=work)
+    t.start()
+    try:
+        while count[0] == 0:
+            stop.wait(0.01)
+        before = count[0]
+        for _ in range(8):
+            st = short.solve()
+        meanwhile = count[0] - before
+    finally:
+        stop.set()
+        t.join()
+    assert st["iters"] == alone["iters"] and np.array_equal(x, short.x.cpu().numpy())
+    assert meanwhile <= 4, f"{meanwhile} long solves ended during 8 short ones"
