@@ -210,6 +210,11 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
     };
     r = launch_links(g, sigma, ws, HUB_F64, st);
     if (r != HUB_OK) return r;
+    // What the caller has queued on its stream ends before the lock is taken:
+    // other threads' solves do not wait for it (a solve of 2 ms beside a thread
+    // with 260 ms queued: 241 ms, and 4 with the wait here), nor for what it may
+    // wait for itself.
+    HUB_HIP(hipStreamSynchronize(st));
     HUB_HIP(hipEventRecord(host.t0, st));
     int done = kRunning, recomputes = 0;
     while (done == kRunning) {

@@ -65,3 +65,36 @@ def test_short_solve_beside_a_long_one():
         t.join()
     assert st["iters"] == alone["iters"] and np.array_equal(x, short.x.cpu().numpy())
     assert meanwhile <= 4, f"{meanwhile} long solves ended during 8 short ones"
+
+
+def test_solve_beside_a_busy_stream():
+    """A thread whose stream has long work queued before its solve keeps no other
+    thread's solve waiting for that work."""
+    import torch
+    hubtest.log_case("cg threads: busy stream")
+    late, other = Problem((3, 8, 80), 500), Problem((3, 8, 80), 500)
+    late.solve(), other.solve()
+    load = torch.ones(1 << 27, device="cuda:0")
+    torch.cuda.synchronize()
+    queued = threading.Event()
+    ready = torch.cuda.Event()
+
+    def work():
+        with torch.cuda.stream(late.stream):
+            for _ in range(2000):  # about 0.3 s
+                load.mul_(1.0)
+            ready.record()
+        queued.set()
+        late.solve()
+
+    t = threading.Thread(target=work)
+    t.start()
+    try:
+        queued.wait()
+        threading.Event().wait(0.02)  # the other thread is in its solve
+        other.solve()
+        pending = not ready.query()
+    finally:
+        t.join()
+    assert pending, "the solve ended only after the other stream's work"
+    assert np.array_equal(late.x.cpu().numpy(), other.x.cpu().numpy())
