@@ -130,7 +130,7 @@ HUB_API hub_status hub_apply_MtM(const hub_lattice* lat, const void* links,
  * Convergence is always decided on the FP64 true residual.  With bulk =
  * HUB_F64 a lattice of at most 2048 sites is solved in one workgroup (one
  * kernel launch), and one that fits the registers of the chip by one block per
- * CU, a launch per 1000 iterations; such launches of several threads follow
+ * CU, a launch per 300 iterations; such launches of several threads follow
  * each other.  There beta is taken from a square expanded before the new
  * residual exists (one grid sum an iteration), and a true residual that
  * replaces the iterated one starts the directions anew; otherwise the

@@ -109,9 +109,14 @@ __global__ __launch_bounds__(256) void k_res_recompute_finish(const double* part
     if (threadIdx.x == 0) st->rho_true = tot[0];
 }
 
-// Products with Q of one launch: about 5 ms, after which other streams and threads
-// get the chip; the state goes through memory in between, some 30 us.
-constexpr int kResChunk = 1000;
+// Products with Q of one launch: 1 to 2 ms.  The blocks fill the registers or the
+// LDS of their CUs, so that a kernel of another stream which does not fit beside
+// them, or whose stream shares a hardware queue with this one, starts only
+// between launches.  A product on 16^3 x 32 beside a solve on 16^3 x 128 waited
+// for 5.9 ms at most with 1000 products a launch and for 1.8 with 300 (with the
+// multi-kernel solver for 0.9 to 1.9 where the queue was shared, else for 0.1).
+// A launch costs some 50 us: solves alone take 2 to 3% more than with 1000.
+constexpr int kResChunk = 300;
 
 // Reads of a grid sum's slots before a wait is given up (about half a second).
 int res_read_limit() {
@@ -183,7 +188,7 @@ hub_status cg_solve_resident(const Geom& g, const double* sigma, const double* p
     a.x = x;
     a.tol2 = o.tol * o.tol;
     a.max_iter = o.max_iter;
-    a.iters = std::max(2, kResChunk / (2 * nf + 1));
+    a.iters = std::max(1, kResChunk / (2 * nf + 1));
     a.mode = kResFirst;
     a.limit = res_read_limit();
     static_assert(sizeof(ResState) <= sizeof(CGScalars), "snapshot buffer");
