@@ -125,11 +125,8 @@ int res_read_limit() {
 }
 
 bool res_enabled() {
-    static const bool v = [] {
-        const char* e = std::getenv("HUB_CG_RESIDENT");
-        return !(e && e[0] == '0');
-    }();
-    return v;
+    const char* e = std::getenv("HUB_CG_RESIDENT");
+    return !(e && e[0] == '0');
 }
 
 }  // namespace
