@@ -129,14 +129,20 @@ HUB_API hub_status hub_apply_MtM(const hub_lattice* lat, const void* links,
  *   solution and r is replaced by the FP64 true residual phi - Q x.
  * Convergence is always decided on the FP64 true residual.  With bulk =
  * HUB_F64 a lattice of at most 2048 sites is solved in one workgroup (one
- * kernel launch), and one that fits the registers of the chip by one block per
- * CU, a launch per 300 iterations; such launches of several threads follow
- * each other.  There beta is taken from a square expanded before the new
- * residual exists (one grid sum an iteration), and a true residual that
- * replaces the iterated one starts the directions anew; otherwise the
- * arrangement is Hestenes and Stiefel's, and the direction is kept.
- * Otherwise, and where the resident solve breaks down, each
- * iteration is a few kernels replayed in chunks from HIP graphs.  The device
+ * kernel launch), with Hestenes and Stiefel's arrangement of the sums.  A larger
+ * one whose vectors and halos fit the registers and LDS of the chip, one block
+ * per CU, stays there, a launch per 300 iterations: d = 1 up to 1 million sites,
+ * d = 2 up to 0.9 to 1 million for nx <= 128, 600 000 for nx = 200, two slices
+ * for nx = 512 and none above, d = 3 up to 384 slices for nx = 12, 192 for nx =
+ * 16, 56 to 46 for nx = 17 to 22 and none above (on 256 CUs).  There beta is
+ * taken from the expanded square of the residual to come (one grid sum an
+ * iteration), and a true residual that replaces the iterated one starts the
+ * directions anew; the other solvers keep the direction.  Such launches of
+ * several threads follow each other in the order in which they come, and a
+ * kernel of another stream that finds no room beside one waits for its end, 1 to
+ * 2 ms.  Otherwise, and where a resident solve breaks down or its blocks do not
+ * all find a place within about half a second, each iteration is a few kernels
+ * replayed in chunks from HIP graphs.  The device
  * workspace (about six V-vectors) and the chunk graphs are kept per
  * host thread after the call: the next solve on that thread reuses the
  * workspace when it is large enough (else frees it and allocates a larger
@@ -198,7 +204,8 @@ HUB_API hub_status hub_apply_cheb_noalloc(const hub_lattice* lat, const double* 
  * |r| <= tol |phi| and confirmed on the FP64 true residual; a failed
  * confirmation restarts from the true residual.  stats->iters counts CG
  * iterations (each costs 2n + 1 applications of Q).  Runs resident on the chip
- * where hub_cg_solve would, and on smaller lattices.  Blocks until done; keeps
+ * where hub_cg_solve would (300 applications of Q a launch), and on smaller
+ * lattices.  Blocks until done; keeps
  * its workspace and graphs, and returns, as hub_cg_solve. */
 HUB_API hub_status hub_pcg_solve(const hub_lattice* lat, const double* sigma,
                          const double* phi, double* x, const hub_cg_opts* opts,
