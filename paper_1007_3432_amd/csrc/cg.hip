@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void k_phaseB_fused(const CGScalars* __restric
                                                       int n_pq, Vec* __restrict__ r,
                                                       const Vec* __restrict__ q, int V,
                                                       double* dep_rr) {
-    phaseB_fused<Vec>(sc_in, sc_out, dep_pq, n_pq, r, q, V, dep_rr, blockIdx.x);
+    phaseB_fused<Vec, true>(sc_in, sc_out, dep_pq, n_pq, r, q, V, dep_rr, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_phaseB_finish_to(const CGScalars* __restrict__ sc_in,
