@@ -171,14 +171,14 @@ static hub_status apply_M_t(const Geom& g, Lnk lk, const void* x, void* y,
 }
 
 // FP64 with even nx: two sites per lane (every row, hence V, is even).
-template <bool TRANSPOSE>
+template <bool TRANSPOSE, bool ONCE>
 static void apply_M2_d(const Geom& g, const double* A, const double* x, double* y,
                        hipStream_t st) {
     const int grid = ceil_div(g.V / 2, 256);
     switch (g.d) {
-        case 1: k_apply_M2<TRANSPOSE, 1><<<grid, 256, 0, st>>>(g, A, x, y); break;
-        case 2: k_apply_M2<TRANSPOSE, 2><<<grid, 256, 0, st>>>(g, A, x, y); break;
-        default: k_apply_M2<TRANSPOSE, 3><<<grid, 256, 0, st>>>(g, A, x, y); break;
+        case 1: k_apply_M2<TRANSPOSE, 1, ONCE><<<grid, 256, 0, st>>>(g, A, x, y); break;
+        case 2: k_apply_M2<TRANSPOSE, 2, ONCE><<<grid, 256, 0, st>>>(g, A, x, y); break;
+        default: k_apply_M2<TRANSPOSE, 3, ONCE><<<grid, 256, 0, st>>>(g, A, x, y); break;
     }
 }
 
@@ -194,10 +194,10 @@ hub_status launch_apply_M(const Geom& g, const void* links, hub_dtype link,
                           hub_dtype vec, const void* x, void* y, int transpose,
                           hipStream_t st) {
     if (vec == HUB_F64 && (g.nx & 1) == 0) {
-        if (transpose)
-            apply_M2_d<true>(g, (const double*)links, (const double*)x, (double*)y, st);
-        else
-            apply_M2_d<false>(g, (const double*)links, (const double*)x, (double*)y, st);
+        const auto run = load_once(g)
+                             ? (transpose ? apply_M2_d<true, true> : apply_M2_d<false, true>)
+                             : (transpose ? apply_M2_d<true, false> : apply_M2_d<false, false>);
+        run(g, (const double*)links, (const double*)x, (double*)y, st);
         HUB_HIP(hipGetLastError());
         return HUB_OK;
     }

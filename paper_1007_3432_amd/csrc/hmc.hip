@@ -67,12 +67,12 @@ __global__ __launch_bounds__(256) void k_force(Geom g, double* __restrict__ sigm
 
 // The same force for even nx, two x-adjacent sites per lane (16-byte loads
 // and stores, the force's with the non-temporal hint for the reason given at
-// k_apply_M: the same buffers again, d = 1 2048 x 512 5.6 -> 4.9 us, d = 3 32^3 x
-// 256 34.8 -> 34.4, buffers in turn 7.7 -> 6.7 and 53 -> 33; with the hint on
-// the loads of sigma too 6.2 and 43, 6.8 and 43; the x neighbours of the pair are
-// its own two values and one more site on each side).  Each site's arithmetic is
-// that of k_force, in the same order.
-template <int MODE, int D>
+// k_apply_M, sigma's load by load_once unless sigma is written back: us, plain
+// and now, the same buffers again, d = 1 2048 x 512 5.6 and 4.9, d = 3 32^3 x 256
+// 35 and 35, 800 MB of buffers in turn 7.3 and 6.9, 52 and 51; the x neighbours of
+// the pair are its own two values and one more site on each side).  Each site's
+// arithmetic is that of k_force, in the same order.
+template <int MODE, int D, bool ONCE>
 __global__ __launch_bounds__(256) void k_force2(Geom g, double* __restrict__ sigma,
                                                 const double* __restrict__ x,
                                                 double* __restrict__ out, double c, double eps) {
@@ -107,7 +107,9 @@ __global__ __launch_bounds__(256) void k_force2(Geom g, double* __restrict__ sig
         rest = q;
     }
     const double sg = sp == 0 ? g.lscale : -g.lscale;
-    const double2 sv = ld2v(sigma + i), xi = ld2v(x + i);
+    const double2 xi = ld2v(x + i);
+    const D2 so = ld2_once<ONCE>(sigma + i);
+    const double2 sv = make_double2(so.a, so.b);
     double sn_a, cs_a, sn_b, cs_b;
     sincos(sv.x, &sn_a, &cs_a);
     sincos(sv.y, &sn_b, &cs_b);
@@ -171,8 +173,11 @@ hub_status launch_force(const Geom& g, int mode, double* sigma, const double* x,
     const int grid = pairs ? ceil_div(g.V / 2, 256) : ceil_div(g.V, 256);
 #define HUB_FORCE(M, D)                                                          \
     do {                                                                         \
-        if (pairs)                                                               \
-            k_force2<M, D><<<grid, 256, 0, st>>>(g, sigma, x, out, c, eps);      \
+        if (pairs && M != kKickDrift && load_once(g))                            \
+            k_force2<M, D, M != kKickDrift>                                      \
+                <<<grid, 256, 0, st>>>(g, sigma, x, out, c, eps);                \
+        else if (pairs)                                                          \
+            k_force2<M, D, false><<<grid, 256, 0, st>>>(g, sigma, x, out, c, eps); \
         else                                                                     \
             k_force<M, D><<<grid, 256, 0, st>>>(g, sigma, x, out, c, eps);       \
     } while (0)

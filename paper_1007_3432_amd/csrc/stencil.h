@@ -1463,16 +1463,28 @@ __global__ __launch_bounds__(256) void k_gen_pass2(Geom g, Op op,
 }
 
 // ---------------------------------------------------------------------------
+// Whether a kernel of two FP64 inputs, one of which it reads once at each site,
+// loads that one with the non-temporal hint: where the two exceed the 256 MB
+// Infinity Cache.  Up to there a call on the same inputs again finds them in it
+// without the hint: M^T, us, without and with, d = 1 2048 x 512 3.7 and 5.4, d = 3
+// 32^3 x 256 29 and 40, x 512 55 and 80, x 600 95 and 89, 64^3 x 80 106 and 100;
+// on inputs that come from HBM (800 MB of buffers in turn) 6.3 and 6.2, 47 and 45,
+// 86 and 82, 97 and 95, 111 and 103.
+inline bool load_once(const Geom& g) { return 16ll * g.V > (256ll << 20); }
+
+template <bool ONCE>
+__device__ __forceinline__ D2 ld2_once(const double* p) {
+    return ONCE ? ld2_nt(p) : ld2(p);
+}
+
 // Single M or M^T (hub_apply_M): one lane per site, neighbours through L1/L2.
 // Bound by memory: the result is stored with the non-temporal hint, so that the
 // caches keep the inputs, which neighbouring blocks (and often the next call)
 // read again.  M^T in FP64, plain stores and now, us: the same buffers again, d =
-// 1 2048 x 512 4.2 -> 3.7, d = 3 16^3 x 160 4.1 -> 3.7, 32^3 x 256 30.3 -> 30.3;
-// buffers taken in turn (700 MB of them; of 32^3 x 256 the inputs then stay in
-// the Infinity Cache) 7.2 -> 6.1, 5.8 -> 5.4, 50 -> 29.  What reads the result
-// next finds it in HBM: M and then M^T 8.4 -> 7.0, 7.5 -> 7.1, but 58 -> 75.
-// (The hint on the loads of the links as well made a call on the same buffers 5.0,
-// 4.8 and 40.8, without being faster on others: 6.1, 5.2 and 40.)
+// 1 2048 x 512 4.2 and 3.7, d = 3 16^3 x 160 4.0 and 3.6, 32^3 x 256 29 and 29, x
+// 512 85 and 55; 800 MB of buffers in turn 6.7 and 6.3, 5.5 and 5.4, 48 and 47, 86
+// and 86.  What reads the result next finds it in HBM: M and then M^T 8.4 and 7.0,
+// 7.5 and 7.1, but 58 and 75 (32^3 x 256).
 template <class Acc, class Vec, class Lnk, bool TRANSPOSE>
 __global__ __launch_bounds__(256) void k_apply_M(Geom g, Lnk lk, const Vec* x, Vec* y) {
     const int i = xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
@@ -1503,7 +1515,7 @@ __global__ __launch_bounds__(256) void k_apply_M(Geom g, Lnk lk, const Vec* x, V
 
 // The same in FP64 for even nx, two x-adjacent sites per lane with 16-byte
 // accesses; each site's arithmetic is that of k_apply_M, in the same order.
-template <bool TRANSPOSE, int D>
+template <bool TRANSPOSE, int D, bool ONCE>
 __global__ __launch_bounds__(256) void k_apply_M2(Geom g, const double* __restrict__ A,
                                                   const double* __restrict__ x,
                                                   double* __restrict__ y) {
@@ -1538,13 +1550,13 @@ __global__ __launch_bounds__(256) void k_apply_M2(Geom g, const double* __restri
     double vb = xc.b - g.kappa * hop_b;
     if (!TRANSPOSE) {
         const int sm = s == 0 ? g.nt - 1 : s - 1;
-        const D2 a = ld2(A + i), xm = ld2(x + n + sm * g.vs);
+        const D2 a = ld2_once<ONCE>(A + i), xm = ld2(x + n + sm * g.vs);
         va += a.a * xm.a;
         vb += a.b * xm.b;
     } else {
         const int sp = s == g.nt - 1 ? 0 : s + 1;
         const int ip = n + sp * g.vs;
-        const D2 a = ld2(A + ip), xp = ld2(x + ip);
+        const D2 a = ld2_once<ONCE>(A + ip), xp = ld2(x + ip);
         va += a.a * xp.a;
         vb += a.b * xp.b;
     }
