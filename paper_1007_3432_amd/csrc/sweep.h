@@ -215,16 +215,31 @@ inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false) {
                 case 16: v = f64 ? kD3_16x8x4_512 : kD3_16x4x4; break;
                 // Eight planes of z a tile wherever its blocks fill the chip
                 // (a lane's four sites in z give each other their neighbours):
-                // bare FP64 product, 32x8x4 and 32x8x8, 32^3 x 256 52.0 and
-                // 48.4 us, x 144 35.7 and 26.4, x 32 10.2 and 9.3, x 20 8.3 and
-                // 8.5, x 8 6.4 and 8.1; FP32 x 256 24.5 and 21.5, x 20 6.4 and
-                // 6.6.  (x 128, whose 32x8x4 march is the unrolled one: 23.7
-                // and 24.4, in FP32 17.0 and 14.2.)
-                case 32:
+                // bare product, 32x8x4 and 32x8x8, us: FP64 32^3 x 16 6.9 and
+                // 8.6, x 24 7.9 and 8.5, x 25 8.9 and 8.5, x 64 16.4 and 14.4, x
+                // 144 34.7 and 26.1, x 256 40 and 40; FP32 x 24 6.3 and 6.5, x 25
+                // 6.9 and 6.6, x 256 24 and 20.6, x 257 33 and 31.  In FP64 a CU
+                // holds one block of it, and two of 32x8x4, which fill the last
+                // turn better: x 257 53 and 66, x 384 57 and 68, x 400 69 and 69,
+                // x 512 73 and 76, x 513 86 and 100, x 640 116 and 126, but x 641
+                // 129 and 124, x 768 138 and 131, x 900 174 and 164.
+                case 32: {
+                    const int last = (ceil_div(g.nt, 16) - 1) % 16;  // of 16 chunks a turn
+                    const bool tall = g.nt >= 25 && (!f64 || g.nt <= 256 ||
+                                                     (g.nt > 512 && last >= 8));
                     if (solve) v = f64 ? kD3_32x8x8_512 : kD3_32x8x4;
-                    else v = g.nt >= 24 ? kD3_32x8x8_512 : kD3_32x8x4_512;
+                    else v = tall ? kD3_32x8x8_512 : kD3_32x8x4_512;
                     break;
-                case 64: v = f64 || !solve ? kD3_64x4x4_512 : kD3_64x4x4; break;
+                }
+                // Bare FP32 products on 512 lanes, unless the second chunk of 16
+                // slices of their unrolled march would repeat half the first: 256
+                // and 512 lanes, us, 64^3 x 16 18.1 and 17.6, x 17 19.2 and 25.8,
+                // x 20 20.3 and 25.3, x 24 23.4 and 24.6, x 28 25.6 and 24.7, x 32
+                // 28.4 and 25.1, x 33 43 and 38, x 64 51 and 47.
+                case 64:
+                    v = f64 || (!solve && (g.nt <= 16 || g.nt >= 26)) ? kD3_64x4x4_512
+                                                                      : kD3_64x4x4;
+                    break;
                 default: v = -1;
             }
         }
