@@ -169,7 +169,7 @@ hub_status launch_cheb(const Geom& g, const SweepPlan& P, const double* A64, CGS
 
 hub_status cheb_apply(const Geom& g, const double* links, const double* r, double* z,
                       const hub_cheb_opts& c, hipStream_t st) {
-    const SweepPlan P = plan_sweep(g, true);
+    const SweepPlan P = plan_sweep(g, true, false, true);
     const double scale = c.scale > 0 ? c.scale : cheb_default_scale(g);
     ChebFactor f[kMaxChebN];
     cheb_factors(c.n, c.eps, scale, f);
@@ -229,7 +229,7 @@ hub_status noalloc_scratch(double** out) {
 }  // namespace
 
 size_t cheb_noalloc_bytes(const Geom& g) {
-    const SweepPlan P = plan_sweep(g, true);
+    const SweepPlan P = plan_sweep(g, true, false, true);
     const size_t vb = ((size_t)g.V * 8 + 255) & ~size_t(255);
     // One vector for the d = 1 and d = 3 tiles, two for the rest: the sizes
     // that callers are told, also where the sweep needs only one.
@@ -247,7 +247,7 @@ hub_status cheb_apply_noalloc(const Geom& g, const double* links, const double* 
     double* ws = nullptr;
     hub_status s = noalloc_scratch(&ws);
     if (s != HUB_OK) return s;
-    const SweepPlan P = plan_sweep(g, true);
+    const SweepPlan P = plan_sweep(g, true, false, true);
     const double scale = c.scale > 0 ? c.scale : cheb_default_scale(g);
     ChebFactor f[kMaxChebN];
     cheb_factors(c.n, c.eps, scale, f);

@@ -143,7 +143,7 @@ inline void plan_rows(const Geom& g, SweepPlan* p) {
                                      : rows_lds_elems<2>(g.nx, ty, tz);
             if (8 * lds > kRowsLdsMax) continue;  // FP64 also in the mixed solver
             // Where the halo is over three times the tile, two passes read less
-            // (d = 3 90^3 x 6 64.0 us against 60.0, 48^3 x 48 42.2 against 76.0).
+            // (d = 3 90^3 x 6 64.0 us against 60.0; see also rows_pay).
             if (hx > 3 * own) continue;
             const int tiles = cy * cz;
             // About two blocks per CU, chunks of 2 to 16 slices (256, 768 and
@@ -173,10 +173,45 @@ inline void plan_rows(const Geom& g, SweepPlan* p) {
     }
 }
 
+// Whether the row tiles of plan_rows are faster than two passes: the time of a
+// block's march, X = turns * (slices + 1) * positions of a lane, against a line in
+// the number of sites.  A turn is as many blocks as the chip holds: two per CU of
+// those that need at most 128 registers a lane, else one.  (Taken as two for all
+// of them, FP64 solves and Chebyshev factors came to the row tiles where they
+// are up to 1.9 times slower, d = 3 72^3 x 7, and bare products up to 1.5 times.)
+// The lines are drawn so that none of 230 to 340 lattices measured (d = 2 with nx
+// = 5 to 1024, d = 3 with nx = 3 to 128, 2 to 600 slices) is over 4% slower
+// than in two passes.  us, two passes and row tiles: bare FP64 products, the two
+// passes with their scratch vector, 63^3 x 17 92 and 70, 67^3 x 17 69 and 76,
+// factors 29^3 x 40 15.7 and 17.0 a sweep, x 100 43 and 35, FP64 CG 40^3 x 7 25
+// and 28 an iteration, x 17 45 and 43; FP32 CG 72^3 x 3 107 and 86, x 7 85 and 93.
+inline bool rows_pay(const Geom& g, const SweepPlan& p, bool f64, bool solve, bool factor) {
+    const RowsLevel& K = kRowsLevels[p.variant];
+    const bool bare = !solve && !factor, d2 = g.d == 2;
+    bool two = true;  // blocks per CU
+    switch (p.variant) {
+        case 0: break;
+        case 1: two = d2 || bare || !f64; break;
+        case 2: two = bare ? !f64 || d2 : !f64 && d2; break;
+        default: two = false;
+    }
+    const double V = g.V;
+    double x = std::ceil(p.grid / (two ? 512.0 : 256.0)) * (p.tc + 1) *
+               (3 * K.own + K.halo_x + 2 * K.halo_y + 2);
+    if (bare) return x <= 112 + 1.4e-4 * V;
+    if (!f64) return x <= 40 + 2.2e-4 * V;
+    // Two blocks share their CU; the largest phase A spills.
+    if (two && p.grid > 256) x *= 1.3;
+    if (solve && p.variant == 3) x *= 1.3;
+    // (From some 2.5 million sites on two passes go to HBM.)
+    return x <= 28 + (V > 2.5e6 ? 1.3e-4 : 1.0e-4) * V;
+}
+
 // f64: the sweep's ops are FP64 throughout, so the pair tile may serve d = 1.
 // solve: the plan of a solver (CG phase A and the true residual), which may
-// take another d = 3 tile than the bare product.
-inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false) {
+// take another d = 3 tile than the bare product.  factor: of a Chebyshev factor's
+// sweeps, which have their scratch vector anyway.
+inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false, bool factor = false) {
     SweepPlan p{};
     p.kind = kSweepGeneric;
     p.variant = -1;
@@ -272,7 +307,7 @@ inline SweepPlan plan_sweep(const Geom& g, bool f64, bool solve = false) {
             plan_rows(g, &q);
             last = {g.d, g.nx, g.nt, q};
         }
-        p = last.p;
+        if (last.p.kind == kSweepRows && rows_pay(g, last.p, f64, solve, factor)) p = last.p;
     }
     if (p.kind == kSweepGeneric) p.ntiles = p.grid = ceil_div(g.V, 256);
     p.fused = p.kind != kSweepGeneric;
