@@ -80,14 +80,14 @@ __global__ __launch_bounds__(256) void k_phaseB(const CGScalars* sc, Vec* __rest
     deposit<256, 1>(part, partials, blockIdx.x);
 }
 
-template <class Vec>
+template <class Vec, int EXIT>
 __global__ __launch_bounds__(256) void k_phaseB_fused(const CGScalars* __restrict__ sc_in,
                                                       CGScalars* __restrict__ sc_out,
                                                       const double* __restrict__ dep_pq,
                                                       int n_pq, Vec* __restrict__ r,
                                                       const Vec* __restrict__ q, int V,
                                                       double* dep_rr) {
-    phaseB_fused<Vec, true>(sc_in, sc_out, dep_pq, n_pq, r, q, V, dep_rr, blockIdx.x);
+    phaseB_fused<Vec, EXIT>(sc_in, sc_out, dep_pq, n_pq, r, q, V, dep_rr, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_phaseB_finish_to(const CGScalars* __restrict__ sc_in,
@@ -286,8 +286,9 @@ struct Solver {
                     HUB_TRY(next_sweep<kByWave>(opA, ne));
                 else
                     HUB_TRY(next_sweep<kByBlock>(opA, ne));
-                k_phaseB_fused<Vec><<<ne, 256, 0, st>>>(sc, sc + 1, partials, P.ntiles, r, q,
-                                                        g.V, dep_rr);
+                const auto phase_b = ne > kFewTiles ? k_phaseB_fused<Vec, kExitBeforeLoads>
+                                                    : k_phaseB_fused<Vec, kExitBeforeSum>;
+                phase_b<<<ne, 256, 0, st>>>(sc, sc + 1, partials, P.ntiles, r, q, g.V, dep_rr);
                 if (next == kByNone || k == iters - 1)
                     k_phaseB_finish_to<<<1, 256, 0, st>>>(sc + 1, sc, dep_rr, ne);
             }

@@ -218,12 +218,20 @@ __device__ __forceinline__ void tile_fold(double* __restrict__ x, float* __restr
 // p.q deposits (the order of reduce_deposits<256, 1>), sets alpha = rho/p.q,
 // then r -= alpha q and r.r deposits.  The block of tile 0 writes the state to
 // sc_out.  Blocks of 256 lanes, one for each of the tiles.
-// EXIT: a solve that has ended returns before the sum.  That costs a running
-// one nothing where it has the chip to itself, and a call of few iterations, most
-// of whose two chunks then find the solve ended, 45 to 65 us less (d = 3 32^3 x
-// 40 to 0.3: 808 -> 758 us); with the blocks of several served solves in turn it
-// is up to 1% slower, 16 small ones 5%.
-template <class Vec, bool EXIT>
+// EXIT: where a block of a solve that has ended returns.  A chunk of iterations
+// goes on after the end of its solve, and after a residual of the mixed solver
+// that has dropped far enough for the next reliable update, so that such blocks
+// can be as many as the others.  Up to kFewTiles tiles the loads of r and q go out
+// before the state is looked at, which a running solve gains by (FP32, 400
+// iterations of 256 x 128 3755 -> 3615 us, of 20^3 x 96 6786 -> 6725).  From there
+// on the loads of an ended solve cost more: to a residual of 0.3, before and after
+// the loads, FP64 32^3 x 64 637 and 786 us, x 256 1080 and 2800, FP32 128^3 x 3, 61
+// iterations with 13 updates, 20.0 and 24.4 ms.  With the blocks of several served
+// solves in turn the return comes last: before the sum it is up to 1% slower, for
+// 16 small ones 5%.
+constexpr int kFewTiles = 512;
+enum BExit { kExitLast = 0, kExitBeforeSum, kExitBeforeLoads };
+template <class Vec, int EXIT>
 __device__ __forceinline__ void phaseB_fused(const CGScalars* __restrict__ sc_in,
                                              CGScalars* __restrict__ sc_out,
                                              const double* __restrict__ dep_pq, int n_pq,
@@ -235,6 +243,10 @@ __device__ __forceinline__ void phaseB_fused(const CGScalars* __restrict__ sc_in
     if (writes) w = reinterpret_cast<const uint64_t*>(sc_in)[threadIdx.x];
     const double rho = sc_in->rho;
     const int was = sc_in->done, updates = sc_in->reliable_updates;
+    if (EXIT == kExitBeforeLoads && was != kRunning) {
+        if (writes) reinterpret_cast<uint64_t*>(sc_out)[threadIdx.x] = w;
+        return;
+    }
     const int base = lane_base(tile), cnt = lane_count(base, V);
     Vec rv[8], qv[8];
     if (cnt == 8) {
@@ -247,7 +259,7 @@ __device__ __forceinline__ void phaseB_fused(const CGScalars* __restrict__ sc_in
             qv[k] = k < cnt ? q[base + eoff(k)] : (Vec)0;
         }
     }
-    if (EXIT && was != kRunning) {
+    if (EXIT == kExitBeforeSum && was != kRunning) {
         if (writes) reinterpret_cast<uint64_t*>(sc_out)[threadIdx.x] = w;
         return;
     }

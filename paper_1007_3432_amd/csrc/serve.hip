@@ -427,7 +427,7 @@ __global__ __launch_bounds__(256) void k_serve_B(const SlotDesc* __restrict__ sl
                                                  const int* __restrict__ offs, int n) {
     const int j = slot_of(offs, n, blockIdx.x);
     const SlotDesc& S = slots[j];
-    phaseB_fused<float, false>(S.sc, S.sc2, S.partials, S.sweep_tiles, S.r, S.q, S.g.V, S.dep_rr,
+    phaseB_fused<float, kExitLast>(S.sc, S.sc2, S.partials, S.sweep_tiles, S.r, S.q, S.g.V, S.dep_rr,
                         xcd_remap(blockIdx.x - offs[j], S.elem_tiles));
 }
 
