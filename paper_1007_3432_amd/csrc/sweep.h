@@ -179,11 +179,11 @@ inline void plan_rows(const Geom& g, SweepPlan* p) {
 // those that need at most 128 registers a lane, else one.  (Taken as two for all
 // of them, FP64 solves and Chebyshev factors came to the row tiles where they
 // are up to 1.9 times slower, d = 3 72^3 x 7, and bare products up to 1.5 times.)
-// The lines are drawn so that none of 230 to 340 lattices measured (d = 2 with nx
-// = 5 to 1024, d = 3 with nx = 3 to 128, 2 to 600 slices) is over 4% slower
-// than in two passes.  us, two passes and row tiles: bare FP64 products, the two
-// passes with their scratch vector, 63^3 x 17 92 and 70, 67^3 x 17 69 and 76,
-// factors 29^3 x 40 15.7 and 17.0 a sweep, x 100 43 and 35, FP64 CG 40^3 x 7 25
+// The lines are drawn so that of 230 to 340 lattices measured (d = 2 with nx = 5
+// to 1024, d = 3 with nx = 3 to 128, 2 to 600 slices) none is over 4% slower than
+// in two passes (factors on 4^3 6%).  us, two passes and row tiles: bare FP64
+// products, the two with their scratch vector, 63^3 x 17 92 and 70, 67^3 x 17 69
+// and 76; factors 29^3 x 40 15.7 and 17.0 a sweep, x 100 43 and 35, FP64 CG 40^3 x 7 25
 // and 28 an iteration, x 17 45 and 43; FP32 CG 72^3 x 3 107 and 86, x 7 85 and 93.
 inline bool rows_pay(const Geom& g, const SweepPlan& p, bool f64, bool solve, bool factor) {
     const RowsLevel& K = kRowsLevels[p.variant];
@@ -203,8 +203,8 @@ inline bool rows_pay(const Geom& g, const SweepPlan& p, bool f64, bool solve, bo
     // Two blocks share their CU; the largest phase A spills.
     if (two && p.grid > 256) x *= 1.3;
     if (solve && p.variant == 3) x *= 1.3;
-    // (From some 2.5 million sites on two passes go to HBM.)
-    return x <= 28 + (V > 2.5e6 ? 1.3e-4 : 1.0e-4) * V;
+    // (From some 3.3 million sites on two passes go to HBM.)
+    return x <= 28 + (V > 3.3e6 ? 1.3e-4 : 1.0e-4) * V;
 }
 
 // f64: the sweep's ops are FP64 throughout, so the pair tile may serve d = 1.
