@@ -141,8 +141,9 @@ HUB_API hub_status hub_apply_MtM(const hub_lattice* lat, const void* links,
  * several threads follow each other in the order in which they come, and a
  * kernel of another stream that finds no room beside one waits for its end, 1 to
  * 2 ms.  Otherwise, and where a resident solve breaks down or its blocks do not
- * all find a place within about half a second, each iteration is a few kernels
- * replayed in chunks from HIP graphs.  The device
+ * all find a place within about half a second (and with HUB_CG_RESIDENT=0 in the
+ * environment), each iteration is a few kernels replayed in chunks from HIP
+ * graphs.  The device
  * workspace (about six V-vectors) and the chunk graphs are kept per
  * host thread after the call: the next solve on that thread reuses the
  * workspace when it is large enough (else frees it and allocates a larger

@@ -26,9 +26,12 @@ constexpr size_t kResLdsMax = 160 * 1024;
 // ns a block), barriers, stores and the halo read (0.9 us), and the LDS
 // accesses of the positions that a level's code goes through, 4 cycles each
 // for a wavefront at 2.4 GHz; the levels that do not fit with z whole are at
-// the register limit and measured 1 us slower than that.  Over 70 cuts of ten
-// lattices the estimate was within 0.6 us of the measured time, and the cut
-// chosen within 0.1 us of the best one.  level < 0: the lattice does not fit.
+// the register limit and measured 1 us slower than that.  Fitted over 70 cuts of
+// ten lattices, to within 0.6 us, with one vector more in the lane's registers;
+// as it is now, us an iteration, estimated and measured: d = 1 4096 x 128 4.0 and
+// 4.2, 2048 x 512 4.4 and 4.8, d = 2 33 x 60 3.3 and 3.4, 128 x 60 6.2 and 6.6, d = 3
+// 8^3 x 80 3.3 and 3.3, 16^3 x 128 4.9 and 5.8, x 160 6.3 and 6.4.  level < 0: the
+// lattice does not fit.
 ResPlan plan_resident(const Geom& g, int max_blocks) {
     ResPlan best;
     const int inner = g.vs / g.nx;
